@@ -229,7 +229,9 @@ int dd_detector_nodes(const dd_problem_desc* desc, int64_t* out, int64_t capacit
 /* Upper bound of the device bytes a problem of this descriptor allocates through its
  * allocator: dd_create, a saving dd_forward (or dd_batch_submit) with n_src sources and every
  * optional buffer (initial data, the div-div form R2 / paper-formula gradient, the misfit's
- * weights and partials, a dd_cga run), for admission control.  0 for an invalid descriptor. */
+ * weights and partials, a dd_cga run, the plans of solves that run resident: up to about three million
+ * grid nodes, built by the forward or adjoint call by which they pay), for admission control.  0 for
+ * an invalid descriptor. */
 size_t dd_footprint_bytes(const dd_problem_desc* desc, int32_t n_src);
 
 /* eps, sigma: FEM-node arrays (float32, n_fem_nodes each) on the device.

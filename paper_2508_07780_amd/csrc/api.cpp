@@ -10,12 +10,14 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <new>
 
 #include "cga.hpp"
 #include "initial.hpp"
 #include "paper_grad.hpp"
 #include "dd_common.hpp"
+#include "resident.hpp"
 
 using namespace dd;
 
@@ -27,6 +29,16 @@ struct GraphCache {
   hipEvent_t done = nullptr;
   std::vector<unsigned char> key, last;
   int64_t captures = 0, replays = 0;
+};
+
+// A brick plan on the device (its host lists are dropped once uploaded).
+struct ResDevice {
+  ResPlan plan;
+  int n_blocks = 0;       // 0: none (yet)
+  int64_t asked = 0;      // steps asked for so far
+  bool tried = false;     // built, or found not to fit
+  bool fresh = false;     // its words have not been cleared
+  ResArgs a{};            // list pointers and sizes
 };
 
 struct dd_problem {
@@ -114,6 +126,16 @@ struct dd_problem {
   bool init_on = false, ic_used = false;
   float *init_f0 = nullptr, *init_f1 = nullptr;
   double* ic_acc = nullptr;
+  // resident solves (resident.hpp): the brick plans of the forward and the adjoint with their device arrays; the
+  // exchange's control block and words, the upload of a source's pulse
+  ResDevice res_fwd, res_adj;
+  ResCtl* res_ctl = nullptr;
+  double* res_tab = nullptr;
+  bool res_ready = false;       // the control block has been cleared
+  std::vector<int> res_own_api; // what the plans are built from; empty: not eligible
+  StarValues res_star{};
+  int res_mode = -1;            // DD_RESIDENT: 0 off, 1 from the first call on, 2 as 1 but every launch is called off
+                                // (a test of the last resort); else once the plan pays
   std::string err;
   std::vector<void*> allocs;
   // kernel timing: event pairs around each step launch, per launch kind
@@ -608,6 +630,262 @@ bool tb_adjoint(const dd_problem* p) {
   return p->tb && p->use_stencil && p->fused && !p->overlap && !p->r2 && !p->pg_on && !p->init_on;
 }
 
+// Grids up to this many nodes replay a repeated forward as a graph under DD_GRAPH_AUTO: their
+// steps take a few microseconds, of which the graph saves 0.5-0.9 (none on larger grids).
+constexpr int64_t kGraphAutoNodes = int64_t(1) << 19;
+
+// ---- resident solves ------------------------------------------------------------------------------
+
+// Resident launches in flight on one GPU together have at most a block per CU: with more, each would hold some of the
+// places the other waits for, and be called off.  (Another process's can still be in the way: then the
+// launch's own protocol decides.)  One entry per stream that queued some, the newest last, bounded.
+struct ResFlight {
+  hipStream_t stream;
+  hipEvent_t end;       // after the stream's newest resident launch
+  int blocks;           // of its largest
+};
+struct ResOrder {
+  std::mutex lock;
+  std::vector<ResFlight> flights;
+};
+constexpr size_t kResFlights = 32;
+ResOrder& res_order() {
+  static ResOrder order[64];
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  return order[dev & 63];
+}
+// Held while a call queues resident launches of `blocks` blocks on `st`: the stream first waits for the newest entries
+// that leave it no room and for all before them.
+struct ResQueue {
+  ResOrder* o = nullptr;
+  hipStream_t st;
+  ResFlight mine{};
+  ResQueue(int blocks, hipStream_t s) : st(s) {
+    if (!blocks) return;
+    o = &res_order();
+    o->lock.lock();
+    std::vector<ResFlight>& f = o->flights;
+    mine = {st, nullptr, blocks};
+    int room = device_cus() - blocks;
+    size_t first = f.size();                      // entries from here on may run beside this call's
+    while (first > 0 && (f[first - 1].stream == st || room >= f[first - 1].blocks)) {
+      --first;
+      if (f[first].stream != st) room -= f[first].blocks;
+    }
+    for (size_t i = 0; i < f.size();) {
+      const bool own = f[i].stream == st;
+      if (i < first || own || f.size() >= kResFlights) {
+        (void)hipStreamWaitEvent(st, f[i].end, 0);
+        if (i < first) --first;
+        if (own && i >= first) mine.blocks = std::max(mine.blocks, f[i].blocks);   // may still be running
+        if (mine.end) (void)hipEventDestroy(f[i].end);
+        else mine.end = f[i].end;
+        f.erase(f.begin() + i);
+      } else {
+        ++i;
+      }
+    }
+  }
+  ~ResQueue() {
+    if (!o) return;
+    if ((mine.end || hipEventCreateWithFlags(&mine.end, hipEventDisableTiming) == hipSuccess) &&
+        hipEventRecord(mine.end, st) == hipSuccess)
+      o->flights.push_back(mine);
+    o->lock.unlock();
+  }
+};
+
+// A brick plan and its lists on the device, in one allocation and one copy.  Without memory for them the problem's
+// solves go on by launches.
+int res_create(dd_problem* p, bool adj, ResDevice& r, hipStream_t st) {
+  const bool rec = adj && n_segments(p) > 1;
+  ResPlan& q = r.plan;
+  build_resident(p->d, p->res_own_api, device_cus(), adj, rec, q);
+  if (q.blocks.empty()) return DD_OK;
+  r.a.n_blocks = (int)q.blocks.size();
+  r.a.n_pub = q.n_pub;
+  const StarValues& v = p->res_star;
+  r.a.sk1 = v.k1; r.a.sk6 = v.k6; r.a.sb1 = v.b1; r.a.sb2 = v.b2; r.a.sb4 = v.b4; r.a.sb6 = v.b6; r.a.sb12 = v.b12;
+  std::vector<unsigned char> all;
+  unsigned char* dev = nullptr;
+  size_t at = 0;
+  const auto put = [&](const auto& list, auto& ptr) {
+    const size_t bytes = list.size() * sizeof(list[0]);
+    if (dev) {
+      ptr = reinterpret_cast<std::remove_reference_t<decltype(ptr)>>(dev + at);
+      if (bytes) std::memcpy(all.data() + at, list.data(), bytes);
+    }
+    at += (bytes + 15) / 16 * 16;
+  };
+  for (int pass = 0; pass < 2; ++pass) {       // the size, then the places
+    at = 0;
+    put(q.blocks, r.a.blocks);
+    put(q.sp_meta, r.a.sp_meta);
+    put(q.sp_det, r.a.sp_det);
+    put(q.pub_cell, r.a.pub_cell);
+    put(q.con_word, r.a.con_word);
+    put(q.con_step, r.a.con_step);
+    put(q.con_cell, r.a.con_cell);
+    put(q.con_src, r.a.con_src);
+    put(q.out_cell, r.a.out_cell);
+    put(q.out_idx, r.a.out_idx);
+    put(q.fem_node, r.a.fem_node);
+    if (pass) break;
+    if (int rc = dalloc(p, &dev, at)) return rc;
+    all.resize(at);
+  }
+  if (int rc = dalloc(p, &r.a.xbuf, (size_t)RES_RING * 3 * q.n_pub)) return rc;
+  if (rec)
+    if (int rc = dalloc(p, &r.a.xbuf_rec, (size_t)RES_RING * 3 * q.n_pub)) return rc;
+  if (!p->res_ctl)
+    if (int rc = dalloc(p, &p->res_ctl, 1)) return rc;
+  if (!p->res_tab)
+    if (int rc = dalloc(p, &p->res_tab, p->d.n_steps)) return rc;
+  if (hipMemcpyAsync(dev, all.data(), at, hipMemcpyHostToDevice, st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess)
+    return fail(p, DD_ERR_HIP, "hipMemcpy upload failed");
+  r.n_blocks = r.a.n_blocks;
+  ResPlan kept;                                 // what the launches read
+  kept.adj = adj;
+  kept.rec = rec;
+  kept.max_run = q.max_run;
+  kept.fem_lds = q.fem_lds;
+  kept.fd_cells = q.fd_cells;
+  q = std::move(kept);
+  r.fresh = true;
+  return DD_OK;
+}
+
+// The first use of a plan clears its exchange words (their tags must match no level), the problem's first also the fields,
+// whose FEM-owned inner nodes nothing writes.
+void res_prepare(dd_problem* p, ResDevice& r, hipStream_t st) {
+  if (!r.fresh) return;
+  r.fresh = false;
+  for (unsigned long long* x : {r.a.xbuf, r.a.xbuf_rec})
+    if (x) launch_fill_f32(reinterpret_cast<float*>(x), (int64_t)RES_RING * 6 * r.a.n_pub, 0.f, st);
+  if (p->res_ready) return;
+  launch_fill_f32(reinterpret_cast<float*>(p->res_ctl), sizeof(ResCtl) / 4, 0.f, st);
+  zero_state(p, st);
+  p->res_ready = true;
+}
+
+ResArgs res_args(const dd_problem* p, const ResDevice& r) {
+  ResArgs a = r.a;
+  a.ctl = p->res_ctl;
+  a.need = p->res_mode == 2 ? r.n_blocks + 1 : r.n_blocks;
+  a.wait_ticks = p->res_mode == 2 ? 1000 : 10000000;   // 0.1 s for the blocks to get their places
+  a.run_ticks = 400000000 + 100000 * (long long)p->d.n_steps;   // 4 s and 1 ms per step without an end: given up
+  a.nx = p->nx; a.ny = p->ny; a.nz = p->nz; a.nt = p->d.n_steps;
+  a.N = p->N; a.n_l0 = p->n_l0; a.n_own = p->n_own; a.n_det = p->n_det;
+  for (int b = 0; b < 2; ++b) {
+    a.Efd[b] = p->Efd[b];
+    a.Efem[b] = p->Efem[b];
+  }
+  a.Vfem = p->Vfem;
+  a.iring = p->iring;
+  a.em1 = p->em1; a.c1 = p->c1; a.c2 = p->c2; a.own_grid = p->own_grid;
+  const FdArgs f = fd_base(p);
+  a.nu = f.nu; a.nu2 = f.nu2; a.dt2_h3 = f.dt2_h3; a.abs_mask = f.abs_mask; a.det_mask = f.det_mask;
+  a.top_det = face_lex_index(0, 0, p->nz - 1, p->nx, p->ny, p->nz, f.det_mask);
+  for (int c = 0; c < 3; ++c) { a.blo[c] = f.blo[c]; a.bhi[c] = f.bhi[c]; }
+  a.dt = p->d.dt;
+  a.t_switch = p->d.t_switch;
+  a.tab = p->res_tab;
+  a.dip_idx = -1;
+  a.K = p->d.ckpt_every; a.n_ck = p->n_ck; a.k_tail = last_segment_start(p); a.nseg = n_segments(p);
+  return a;
+}
+
+// Whether a call of n_src solves runs resident on stream st: with the default launch options, and not within
+// a capture of the caller's (whose replays the ordering of resident launches would not see).  The plan is built when
+// the problem has been asked for 100 + N / 2000 steps: it takes 0.2 ms for 25^3, 1.6 ms for 64^3 and 3.3 ms for 96^3, a step gains 2.5 to 5 us, so a
+// first call that builds it (231 steps of 64^3, 543 of 96^3) costs little more than by launches, and a problem that is solved once
+// for a few steps builds none; a caller that asks for graphs says that the call comes
+// again, and one that has repeated a call that a graph would then hold does so too.
+bool res_wanted(dd_problem* p, bool adj, int n_src, bool again, hipStream_t st) {
+  ResDevice& r = adj ? p->res_adj : p->res_fwd;
+  if (p->res_own_api.empty() || !p->res_mode || !p->use_stencil || !p->fused || p->overlap || p->tb || p->r2 || p->init_on ||
+      p->prof_stride > 0)
+    return false;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
+  r.asked = std::min(r.asked + (int64_t)n_src * p->d.n_steps, p->N + 100);
+  if (!r.tried && (p->res_mode > 0 || p->graph == DD_GRAPH_ON || (again && p->N <= kGraphAutoNodes) || 2000 * (r.asked - 100) >= p->N)) {
+    r.tried = true;
+    const std::string err = p->err;
+    if (res_create(p, adj, r, st) != DD_OK) {
+      (void)hipGetLastError();
+      p->err = err;
+    }
+  }
+  return r.n_blocks > 0;
+}
+
+int res_forward(dd_problem* p, const dd_source& src, int s, float* traces, bool save, hipStream_t st) {
+  ResArgs a = res_args(p, p->res_fwd);
+  const SrcPlan sp = source_plan(p, src);
+  const double dt = p->d.dt, h = p->d.h;
+  a.plane = src.kind != DD_SRC_DIPOLE;
+  a.oblique = sp.oblique;
+  a.kind = src.kind;
+  a.pw_scale = 2.0 * dt * dt / h;
+  a.dip_scale = sp.dip_scale;
+  a.dip_idx = sp.dip_idx;
+  for (int c = 0; c < 3; ++c) {
+    a.pol[c] = src.pol[c];
+    a.pw_amp[c] = (float)(2.0 * dt * dt / h * src.amp * src.pol[c]);
+  }
+  a.pw_kx = (float)(sp.kx * h); a.pw_ky = (float)(sp.ky * h);
+  a.pw_x0 = sp.x0; a.pw_y0 = sp.y0;
+  a.pw_omega = (float)src.omega;
+  a.pw_t0 = src.t0;
+  a.pw_iw = src.kind == DD_SRC_GAUSS_SINE ? (float)(1.0 / src.width) : 0.f;
+  a.pw_sup = src.kind == DD_SRC_GAUSS_SINE ? (float)src.t0 : (float)(2.0 * M_PI / src.omega);
+  a.traces = traces + (int64_t)s * p->d.n_steps * p->n_det * 3;
+  if (save) {
+    a.ihist = p->ihist[s];
+    a.ckpt = p->ckpt[s];
+    a.tail = p->tail[s];
+  }
+  // the pulse at every step up to its last nonzero value
+  std::vector<double> tab;
+  if (!sp.oblique)
+    for (int n = 0; n < p->d.n_steps; ++n) {
+      const double v = source_time(src, (double)n * dt);
+      if (v != 0.0) {
+        tab.resize(n, 0.0);
+        tab.push_back(v);
+      }
+    }
+  a.n_tab = (int)tab.size();
+  launch_resident_begin(a, tab.data(), a.n_tab, st);
+  launch_resident(a, p->res_fwd.plan, st);
+  launch_resident_serial(a, fd_base(p), fem_base(p), false, st);
+  return check_launch(p);
+}
+
+int res_adjoint(dd_problem* p, int s, const float* cot, const float* obs, hipStream_t st) {
+  ResArgs a = res_args(p, p->res_adj);
+  const int64_t row = (int64_t)s * p->d.n_steps * p->n_det * 3;
+  a.cot = cot + row;
+  a.obs = obs ? obs + row : nullptr;
+  a.ihist = p->ihist[s];
+  a.ckpt = p->ckpt[s];
+  a.tail = p->tail[s];
+  a.win = p->win;
+  a.win_b = p->win_b;
+  a.g_eps = p->g_eps;
+  a.g_sig = p->g_sig;
+  a.mass_d = p->mass_d;
+  const FemArgs f = fem_base(p);
+  a.inv_dt2 = f.inv_dt2;
+  a.inv_2dt = f.inv_2dt;
+  launch_resident_begin(a, nullptr, 0, st);
+  launch_resident(a, p->res_adj.plan, st);
+  launch_resident_serial(a, fd_base(p), f, true, st);
+  return check_launch(p);
+}
+
 int run_forward(dd_problem* p, const dd_source& src, int s, float* traces, bool save, double* energy, hipStream_t st) {
   const int64_t nt = p->d.n_steps;
   forward_prologue(p, s, save, true, st);
@@ -803,9 +1081,6 @@ void key_put(std::vector<unsigned char>& k, const T& v) {
   k.insert(k.end(), b, b + sizeof(T));
 }
 
-// Grids up to this many nodes replay a repeated forward as a graph under DD_GRAPH_AUTO: their
-// steps take a few microseconds, of which the graph saves 0.5-0.9 (none on larger grids).
-constexpr int64_t kGraphAutoNodes = int64_t(1) << 19;
 
 // What the launches of a dd_forward call depend on besides device memory the problem owns
 // (coefficients, initial data, saved forward): the sources, the caller's buffers, the flags
@@ -823,15 +1098,19 @@ std::vector<unsigned char> forward_key(const dd_problem* p, const dd_source* src
   return key;
 }
 
-// Whether a call with this key replays the graph of `g` (and records the call for
-// DD_GRAPH_AUTO).
-bool graph_wanted(dd_problem* p, GraphCache& g, const std::vector<unsigned char>& key) {
+// Whether a call with this key replays the graph of `g`; again: it is the last call once more.
+bool graph_wanted(dd_problem* p, GraphCache& g, const std::vector<unsigned char>& key, bool again) {
   if (p->graph == DD_GRAPH_OFF || p->overlap || p->prof_stride > 0) return false;
   if (p->graph == DD_GRAPH_ON) return true;
   if (p->N > kGraphAutoNodes) return false;
-  const bool repeat = (g.exec && key == g.key) || key == g.last;
+  return (g.exec && key == g.key) || again;
+}
+// Whether the call before this one had the same key (its route left out).
+bool call_again(const dd_problem* p, GraphCache& g, const std::vector<unsigned char>& key) {
+  if (p->graph == DD_GRAPH_OFF || p->overlap || p->prof_stride > 0) return false;
+  const bool again = key == g.last;
   g.last = key;
-  return repeat;
+  return again;
 }
 
 // The launches `queue` issues on a stream, as one HIP graph: captured on the problem's capture
@@ -1015,6 +1294,9 @@ size_t dd_footprint_bytes(const dd_problem_desc* desc, int32_t n_src) {
   b += (int64_t)n_src * ((nt + 1) * 3 * n_l0 * 4 + (n_ck + tail_levels) * 6 * n_own * 4);  // saved forward
   if (nseg > 1) b += (K + 1) * 6 * n_own * 4;  // recompute window
   if (nseg > 2) b += (K + 1) * 6 * n_own * 4;  // the second one (two segments in flight)
+  // resident solves: brick lists and exchange words, the pulse
+  b += resident_bytes_bound(*desc, device_cus(), false, false) + 8 * nt + 1024;
+  b += resident_bytes_bound(*desc, device_cus(), true, nseg > 1);
   // optional buffers: misfit partials and weights; FEM-node map and sum of the div-div
   // gradient terms (R2 / paper-formula gradient); initial data and its level-0 rows; a CGA run
   b += 8 * 1024 + 8 * nt;
@@ -1171,6 +1453,10 @@ int create_problem(const dd_problem_desc* desc, const MeshInput* gm, dd_alloc_fn
     chk(upload(p, &p->slot_k, m.slot_k));
     chk(upload(p, &p->slot_b, m.slot_b));
   }
+  if (const char* e = std::getenv("DD_RESIDENT")) p->res_mode = std::atoi(e);
+  if (p->use_stencil && !p->tb && p->res_mode) {
+    if (kuhn_star(m, p->res_star) && resident_fits(p->d, device_cus())) p->res_own_api.assign(m.own_api.begin(), m.own_api.end());
+  }
   chk(dalloc(p, &p->em1, p->n_own));
   chk(dalloc(p, &p->c1, p->n_own));
   chk(dalloc(p, &p->c2, p->n_own));
@@ -1325,17 +1611,24 @@ int dd_forward(dd_problem* p, const dd_source* src, int32_t n_src, float* traces
     int rc = ensure_saved_storage(p, n_src);
     if (rc) return rc;
   }
-  const std::vector<unsigned char> key = forward_key(p, src, n_src, traces_dev, save != 0, energy_dev);
-  if (graph_wanted(p, p->gfwd, key)) {
+  std::vector<unsigned char> key = forward_key(p, src, n_src, traces_dev, save != 0, energy_dev);
+  const bool again = call_again(p, p->gfwd, key), res = !energy_dev && res_wanted(p, false, n_src, again, st);
+  key_put(key, res);
+  ResQueue order(res ? p->res_fwd.n_blocks : 0, st);
+  if (res) res_prepare(p, p->res_fwd, st);
+  if (graph_wanted(p, p->gfwd, key, again)) {
     int rc = graph_run(p, p->gfwd, key, st, [&](hipStream_t cs) {
       int r = DD_OK;
-      for (int s = 0; s < n_src && !r; ++s) r = run_forward(p, src[s], s, traces_dev, save != 0, energy_dev, cs);
+      for (int s = 0; s < n_src && !r; ++s)
+        r = res ? res_forward(p, src[s], s, traces_dev, save != 0, cs)
+                : run_forward(p, src[s], s, traces_dev, save != 0, energy_dev, cs);
       return r;
     });
     if (rc) return rc;
   } else {
     for (int s = 0; s < n_src; ++s) {
-      int rc = run_forward(p, src[s], s, traces_dev, save != 0, energy_dev, st);
+      int rc = res ? res_forward(p, src[s], s, traces_dev, save != 0, st)
+                   : run_forward(p, src[s], s, traces_dev, save != 0, energy_dev, st);
       if (rc) return rc;
     }
   }
@@ -1348,13 +1641,13 @@ int dd_forward(dd_problem* p, const dd_source* src, int32_t n_src, float* traces
 
 namespace {
 // The adjoint sweeps of every saved source with their gradient sums cleared first.
-int adjoint_launches(dd_problem* p, const float* cot, const float* obs, hipStream_t st) {
+int adjoint_launches(dd_problem* p, const float* cot, const float* obs, bool res, hipStream_t st) {
   launch_fill_f64(p->g_eps, p->n_own, 0.0, st);
   launch_fill_f64(p->g_sig, p->n_own, 0.0, st);
   if (p->pg_on || p->r2) launch_fill_f64(p->pg_acc, p->n_fem, 0.0, st);
   if (p->ic_used) launch_fill_f64(p->ic_acc, p->n_fem, 0.0, st);
   for (int s = 0; s < p->saved_n_src; ++s) {
-    int rc = run_adjoint(p, s, cot, obs, st);
+    int rc = res ? res_adjoint(p, s, cot, obs, st) : run_adjoint(p, s, cot, obs, st);
     if (rc) return rc;
   }
   return DD_OK;
@@ -1370,18 +1663,22 @@ int adjoint_all(dd_problem* p, const float* cot, const float* obs, hipStream_t s
   // one checkpoint segment only: with several, the recompute runs on a second stream, and a
   // graph with that parallel branch gained nothing and its launch held the host until the
   // stream had drained
-  if (n_segments(p) == 1 && graph_wanted(p, p->gadj, key)) {
+  const bool again = call_again(p, p->gadj, key), res = !p->pg_on && res_wanted(p, true, p->saved_n_src, again, st);
+  key_put(key, res);
+  ResQueue order(res ? p->res_adj.n_blocks : 0, st);
+  if (res) res_prepare(p, p->res_adj, st);
+  if (n_segments(p) == 1 && graph_wanted(p, p->gadj, key, again)) {
     int rc = graph_run(p, p->gadj, key, st, [&](hipStream_t cs) {
-      int r = adjoint_launches(p, cot, obs, cs);
+      int r = adjoint_launches(p, cot, obs, res, cs);
       // the segment recompute stream joined the capture through the sweep's first event
       // wait, with nothing to do in one segment: it rejoins here
-      if (!r && (hipEventRecord(p->ev_fem, p->aux) != hipSuccess || hipStreamWaitEvent(cs, p->ev_fem, 0) != hipSuccess))
+      if (!r && !res && (hipEventRecord(p->ev_fem, p->aux) != hipSuccess || hipStreamWaitEvent(cs, p->ev_fem, 0) != hipSuccess))
         r = fail(p, DD_ERR_HIP, "stream join failed");
       return r;
     });
     if (rc) return rc;
   } else {
-    int rc = adjoint_launches(p, cot, obs, st);
+    int rc = adjoint_launches(p, cot, obs, res, st);
     if (rc) return rc;
   }
   p->have_grad = true;

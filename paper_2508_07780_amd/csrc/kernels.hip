@@ -13,7 +13,9 @@
 //     lambda^{k-1} = lambda^k + Lambda^k.
 // Field state is FP32; the energy and gradient sums are FP64.
 #include "dd_common.hpp"
+#include "oblique.hpp"
 #include "pg_tile.hpp"
+#include "resident.hpp"
 
 namespace dd {
 
@@ -48,23 +50,6 @@ __device__ __forceinline__ void st_own(char* base, uint32_t off, float v) {
   else *reinterpret_cast<float*>(base + off) = v;
 }
 
-// The time function of an obliquely incident plane wave at top-face node (x, y): the pulse of
-// the source kind delayed by tau = pw_kx (x - pw_x0) + pw_ky (y - pw_y0).  Inside the pulse's
-// support the sine's argument stays within 3 pi (the Gaussian-modulated sine: |omega u| <=
-// omega t0 = 3 pi; one sine period: < 2 pi), where the hardware sine and exponential are
-// accurate to about 1e-6, well inside the trace tolerance, and need no argument reduction.
-// kind, tn: the step's source kind and time (t_n, or t_n - t0 for the Gaussian-modulated sine).
-__device__ __forceinline__ float oblique_pulse_at(const FdArgs& a, int kind, float tn, int x, int y) {
-  const float tau = a.pw_kx * (float)(x - a.pw_x0) + a.pw_ky * (float)(y - a.pw_y0);
-  const float u = tn - tau;
-  if (kind == DD_SRC_GAUSS_SINE) {
-    if (!(fabsf(u) <= a.pw_sup)) return 0.f;
-    const float v = u * a.pw_iw;
-    return __sinf(a.pw_omega * u) * __expf(-0.5f * v * v);
-  }
-  if (!(u > 0.f && u < a.pw_sup)) return 0.f;
-  return __sinf(a.pw_omega * u);
-}
 __device__ __forceinline__ float oblique_pulse(const FdArgs& a, int x, int y) {
   return oblique_pulse_at(a, a.pw_kind, a.pw_t, x, y);
 }
@@ -1615,7 +1600,6 @@ size_t fem_lds_bytes(const FemArgs& a, bool adj, bool stage) {
   return f * 4;
 }
 
-namespace {
 int device_cus() {
   static int cus = 0;
   if (!cus) {
@@ -1627,6 +1611,7 @@ int device_cus() {
   return cus;
 }
 
+namespace {
 template <bool ADJ, bool ENERGY, bool GEOM, bool STAGE, bool GATHER = false>
 void launch_fem_v(const FemArgs& a, int n_part, size_t lds, hipStream_t s) {
   if (lds > 65536)
@@ -1863,6 +1848,138 @@ void launch_gradient_out(const double* g_eps, const double* g_sig, const int* ow
 
 void launch_count_nonfinite(const float* x, int64_t n, int* err, hipStream_t s) {
   if (n > 0) hipLaunchKernelGGL(count_nonfinite_kernel, dim3(grid_for(n)), dim3(256), 0, s, x, n, err);
+}
+
+// ---------------------------------------------------------------------------------------
+// A resident solve's last resort (resident.hpp): one block takes every step with the tiles and partitions of the
+// step kernels, one after another, unless the solve is done.  It waits for no other block.  A few
+// hundred times slower than the resident kernel; it only runs where that was called off twice.
+// ---------------------------------------------------------------------------------------
+template <bool ADJ>
+__global__ __launch_bounds__(FD_THREADS) void resident_serial_kernel(ResArgs a, FdArgs fa, FemArgs ea) {
+#pragma clang fp contract(off)
+  if (a.ctl->state == RES_DONE) return;
+  const int tid = threadIdx.x;
+  const int64_t n_own = a.n_own, n_l0 = a.n_l0;
+  auto zero = [&](float* p, int64_t n) {
+    for (int64_t i = tid; i < n; i += FD_THREADS) p[i] = 0.f;
+  };
+  for (int b = 0; b < 2; ++b) {
+    zero(a.Efd[b], 3 * a.N);
+    zero(a.Efem[b], 3 * n_own);
+  }
+  zero(a.Vfem, 3 * n_own);
+  zero(a.iring, 6 * n_l0);
+  if (!ADJ && a.ihist) {
+    zero(a.ihist, 3 * n_l0);
+    zero(a.ckpt, 6 * n_own);
+    if (a.k_tail == 0) zero(a.tail, 6 * n_own);
+  }
+  auto fem = [&](const FemArgs& e, bool adj) {
+    for (int p = 0; p < e.n_part; ++p) {
+      __syncthreads();
+      if (adj) fem_stencil_part<true, false>(e, p);
+      else fem_stencil_part<false, false>(e, p);
+    }
+    __syncthreads();
+  };
+  auto tiles = [&]() {
+    for (int b = 0; b < fa.per_xcd * N_XCD; ++b) {
+      __syncthreads();
+      fd_tile<false, false, true>(fa, b);
+    }
+    __syncthreads();
+  };
+  fa.epart = ea.epart = nullptr;
+  fa.X_prev = nullptr;
+  ea.I_in = ea.I_out = a.Vfem;
+  ea.ck_X = ea.ck_I = nullptr;
+  __syncthreads();
+  if (!ADJ) {
+    for (int n = 0; n < a.nt; ++n) {
+      const int cur = n & 1, nxt = cur ^ 1;
+      const double t = (double)n * a.dt;
+      fa.X_in = a.Efd[cur]; fa.X_out = a.Efd[nxt];
+      fa.rev = ea.rev = 0;
+      fa.top_a = fa.top_b = (a.abs_mask & DD_FACE_TOP) && t > a.t_switch;
+      const double pulse = n < a.n_tab ? a.tab[n] : 0.0;
+      const bool on = a.plane && t <= a.t_switch;
+      for (int c = 0; c < 3; ++c) {
+        fa.pw[c] = on && !a.oblique ? (float)(a.pw_scale * pulse * a.pol[c]) : 0.f;
+        fa.dip[c] = (float)(pulse * a.pol[c] * a.dip_scale);
+        fa.pw_amp[c] = a.pw_amp[c];
+      }
+      fa.dip_idx = a.dip_idx;
+      fa.pw_kind = on && a.oblique ? a.kind : 0;
+      fa.pw_kx = a.pw_kx; fa.pw_ky = a.pw_ky; fa.pw_x0 = a.pw_x0; fa.pw_y0 = a.pw_y0;
+      fa.pw_omega = a.pw_omega; fa.pw_iw = a.pw_iw; fa.pw_sup = a.pw_sup;
+      fa.pw_t = a.kind == DD_SRC_GAUSS_SINE ? (float)(t - a.pw_t0) : (float)t;
+      fa.tr_out = a.traces + (int64_t)n * a.n_det * 3;
+      fa.cot_in = fa.obs_in = nullptr;
+      fa.iface_out = a.ihist ? a.ihist + (int64_t)(n + 1) * 3 * n_l0 : a.iring + nxt * 3 * n_l0;
+      ea.X_in = a.Efem[cur]; ea.X_out = a.Efem[nxt];
+      ea.iface_in = a.ihist ? a.ihist + (int64_t)n * 3 * n_l0 : a.iring + cur * 3 * n_l0;
+      ea.fd_out = a.Efd[nxt];
+      ea.ck_X = nullptr;
+      if (a.ckpt && n + 1 >= a.k_tail) ea.ck_X = a.tail + (n + 1 - a.k_tail) * 6 * n_own;
+      else if (a.ckpt && (n + 1) % a.K == 0 && (n + 1) / a.K < a.n_ck) ea.ck_X = a.ckpt + ((n + 1) / a.K) * 6 * n_own;
+      ea.ck_I = ea.ck_X ? ea.ck_X + 3 * n_own : nullptr;
+      fem(ea, false);
+      tiles();
+    }
+  } else {
+    for (int64_t seg = a.nseg - 1; seg >= 0; --seg) {
+      const int64_t k0 = seg * a.K, k1 = min(k0 + a.K, (int64_t)a.nt);
+      float* win = seg == a.nseg - 1 ? a.tail : (seg & 1) ? a.win_b : a.win;
+      if (seg != a.nseg - 1) {
+        const float* ck = a.ckpt + seg * 6 * n_own;
+        for (int64_t i = tid; i < 6 * n_own; i += FD_THREADS) win[i] = ck[i];
+        FemArgs fw = ea;
+        fw.fd_out = nullptr;
+        fw.ck_X = fw.ck_I = nullptr;
+        for (int64_t k = k0; k < k1; ++k) {
+          fw.X_in = win + (k - k0) * 6 * n_own;
+          fw.X_out = win + (k - k0 + 1) * 6 * n_own;
+          fw.I_in = fw.X_in + 3 * n_own;
+          fw.I_out = fw.X_out + 3 * n_own;
+          fw.iface_in = a.ihist + k * 3 * n_l0;
+          fem(fw, false);
+        }
+      }
+      for (int64_t k = k1; k > k0; --k) {
+        const int cur = (int)(k & 1), prv = cur ^ 1;
+        fa.X_in = a.Efd[cur]; fa.X_out = a.Efd[prv];
+        fa.rev = ea.rev = 0;
+        fa.top_a = (a.abs_mask & DD_FACE_TOP) && (double)(k - 1) * a.dt > a.t_switch;
+        fa.top_b = (a.abs_mask & DD_FACE_TOP) && (double)(k + 1) * a.dt > a.t_switch;
+        for (int c = 0; c < 3; ++c) fa.pw[c] = fa.dip[c] = 0.f;
+        fa.dip_idx = -1;
+        fa.pw_kind = 0;
+        fa.tr_out = nullptr;
+        fa.cot_in = a.cot + (k - 1) * a.n_det * 3;
+        fa.obs_in = a.obs ? a.obs + (k - 1) * a.n_det * 3 : nullptr;
+        fa.iface_out = a.iring + prv * 3 * n_l0;
+        ea.X_in = a.Efem[cur]; ea.X_out = a.Efem[prv];
+        ea.iface_in = a.iring + cur * 3 * n_l0;
+        ea.fd_out = a.Efd[prv];
+        ea.wE = win + (k - k0) * 6 * n_own;
+        ea.wV = ea.wE + 3 * n_own;
+        ea.wVm = win + (k - 1 - k0) * 6 * n_own + 3 * n_own;
+        ea.g_eps = a.g_eps;
+        ea.g_sig = a.g_sig;
+        fem(ea, true);
+        tiles();
+      }
+    }
+  }
+  if (tid == 0) ++a.ctl->serial;
+}
+
+void launch_resident_serial(const ResArgs& a, const FdArgs& fa, const FemArgs& ea, bool adj, hipStream_t s) {
+  if (adj)
+    hipLaunchKernelGGL((resident_serial_kernel<true>), dim3(1), dim3(FD_THREADS), stencil_lds(ea), s, a, fa, ea);
+  else
+    hipLaunchKernelGGL((resident_serial_kernel<false>), dim3(1), dim3(FD_THREADS), stencil_lds(ea), s, a, fa, ea);
 }
 
 }  // namespace dd
