@@ -309,6 +309,7 @@ FdArgs fd_base(const dd_problem* p) {
     a.fs[c] = p->fs[c];
   }
   a.nbx = p->nbx; a.nby = p->nby; a.nbz = p->nbz; a.ntiles = p->n_tiles; a.per_xcd = p->per_xcd;
+  fd_row_grid(a, p->fd_nt);
   const double nu = p->d.dt / p->d.h;
   a.nu = (float)nu;
   a.nu2 = (float)(nu * nu);
@@ -1301,7 +1302,7 @@ size_t dd_footprint_bytes(const dd_problem_desc* desc, int32_t n_src) {
   // gradient terms (R2 / paper-formula gradient); initial data and its level-0 rows; a CGA run
   b += 8 * 1024 + 8 * nt;
   b += (4 + 8) * n_fem;
-  b += 2 * 4 * 3 * N + 8 * n_fem;
+  b += 2 * 4 * (3 * N + FD_PAD) + 8 * n_fem;
   b += (2 * 4 + 2 * 8) * n_fem + 8 * 6 * 1024 + 1024;
   return (size_t)b;
 }
@@ -1462,12 +1463,12 @@ int create_problem(const dd_problem_desc* desc, const MeshInput* gm, dd_alloc_fn
   chk(dalloc(p, &p->c2, p->n_own));
   chk(dalloc(p, &p->sig_own, p->n_own));
   for (int b = 0; b < 2; ++b) {
-    chk(dalloc(p, &p->Efd[b], 3 * p->N));
+    chk(dalloc(p, &p->Efd[b], 3 * p->N + FD_PAD));
     chk(dalloc(p, &p->Efem[b], 3 * p->n_own));
   }
   if (p->tb) {
-    chk(dalloc(p, &p->Efd[2], 3 * p->N));
-    chk(dalloc(p, &p->Efd[3], 3 * p->N));
+    chk(dalloc(p, &p->Efd[2], 3 * p->N + FD_PAD));
+    chk(dalloc(p, &p->Efd[3], 3 * p->N + FD_PAD));
     if (!tb_list.empty()) chk(upload(p, &p->tb_list, tb_list));
   }
   chk(dalloc(p, &p->Vfem, 3 * p->n_own));
@@ -2503,7 +2504,8 @@ int dd_batch_step(dd_batch* b, int32_t max_steps, void* stream) {
         it.fd_blocks = 0;
         if (it.kind != 2) {
           fd_tile_grid(q->nx, q->ny, q->nz, use_nt, it.fa.nbx, it.fa.nby, it.fa.nbz, it.fa.ntiles, it.fa.per_xcd);
-          it.fd_blocks = it.fa.per_xcd * N_XCD;
+          fd_row_grid(it.fa, use_nt);
+          it.fd_blocks = it.fa.row_per_xcd * N_XCD;
         }
         l = std::max(l, stencil_lds(it.ea));
         bases[m].base[i] = base;   // each item's FEM partitions, then its FD tiles

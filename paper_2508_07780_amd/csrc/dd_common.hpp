@@ -39,6 +39,16 @@ __host__ __device__ constexpr int fd_zc(bool nt) { return nt ? FD_ZC_STREAM : FD
 constexpr int FD_ZGROUP = DD_FD_ZGROUP;
 __host__ __device__ constexpr int fd_zgroup(bool nt) { return nt ? FD_ZGROUP : 1; }
 constexpr int FD_THREADS = FD_TX * FD_TY;
+// The four-nodes-per-thread update (steps without energies): planes per block, fields in the last-level cache or
+// streaming (measured at fd_rows).
+#ifndef DD_ROW_ZC
+#define DD_ROW_ZC 2
+#endif
+#ifndef DD_ROW_ZC_NT
+#define DD_ROW_ZC_NT 3
+#endif
+constexpr int FD_PAD = 4;                // floats past a field: a row's last quad reads past its end
+__host__ __device__ constexpr int row_zc(bool nt) { return nt ? DD_ROW_ZC_NT : DD_ROW_ZC; }
 // the FD tile's two LDS planes of three components (when they sit in the dynamic LDS)
 constexpr size_t FD_DYN_LDS_BYTES = sizeof(float) * 2 * 3 * (FD_TY + 2) * (FD_TX + 2);
 // Last-level cache (MI355X Infinity Cache).  A grid whose two levels of E exceed it streams
@@ -68,7 +78,8 @@ constexpr int N_XCD = 8;  // MI355X: workgroups are dispatched round-robin over 
 // Index of node (x, y, z) among the nodes of an nx*ny*nz box that lie on the
 // faces in `mask`, counted in lexicographic order (x fastest); -1 if the node
 // is on none of them.  Requires nx, ny, nz >= 2.
-__host__ __device__ inline int64_t face_lex_index(int x, int y, int z, int nx, int ny, int nz, unsigned mask) {
+template <class Index>   // int64_t, or int on grids of fewer than 2^30 nodes
+__host__ __device__ inline Index face_lex(int x, int y, int z, int nx, int ny, int nz, unsigned mask) {
   const bool zlo = (mask & DD_FACE_BOTTOM) && z == 0;
   const bool zhi = (mask & DD_FACE_TOP) && z == nz - 1;
   const bool xlo = (mask & DD_FACE_XMIN) && x == 0;
@@ -76,17 +87,20 @@ __host__ __device__ inline int64_t face_lex_index(int x, int y, int z, int nx, i
   const bool ylo = (mask & DD_FACE_YMIN) && y == 0;
   const bool yhi = (mask & DD_FACE_YMAX) && y == ny - 1;
   if (!(zlo || zhi || xlo || xhi || ylo || yhi)) return -1;
-  const int64_t cm = ((mask & DD_FACE_XMIN) ? 1 : 0) + ((mask & DD_FACE_XMAX) ? 1 : 0);
-  const int64_t ny_mid = ny - ((mask & DD_FACE_YMIN) ? 1 : 0) - ((mask & DD_FACE_YMAX) ? 1 : 0);
-  const int64_t p_mid = (int64_t)(ny - ny_mid) * nx + ny_mid * cm;
-  const int64_t p_full = (int64_t)nx * ny;
-  int64_t before = 0;
-  if (z > 0) before = ((mask & DD_FACE_BOTTOM) ? p_full : p_mid) + (int64_t)(z - 1) * p_mid;
-  if (zlo || zhi) return before + (int64_t)y * nx + x;
-  int64_t rows = 0;
-  if (y > 0) rows = ((mask & DD_FACE_YMIN) ? (int64_t)nx : cm) + (int64_t)(y - 1) * cm;
+  const Index cm = ((mask & DD_FACE_XMIN) ? 1 : 0) + ((mask & DD_FACE_XMAX) ? 1 : 0);
+  const Index ny_mid = ny - ((mask & DD_FACE_YMIN) ? 1 : 0) - ((mask & DD_FACE_YMAX) ? 1 : 0);
+  const Index p_mid = (Index)(ny - ny_mid) * nx + ny_mid * cm;
+  const Index p_full = (Index)nx * ny;
+  Index before = 0;
+  if (z > 0) before = ((mask & DD_FACE_BOTTOM) ? p_full : p_mid) + (Index)(z - 1) * p_mid;
+  if (zlo || zhi) return before + (Index)y * nx + x;
+  Index rows = 0;
+  if (y > 0) rows = ((mask & DD_FACE_YMIN) ? (Index)nx : cm) + (Index)(y - 1) * cm;
   if (ylo || yhi) return before + rows + x;
   return before + rows + (xlo ? 0 : ((mask & DD_FACE_XMIN) ? 1 : 0));
+}
+__host__ __device__ inline int64_t face_lex_index(int x, int y, int z, int nx, int ny, int nz, unsigned mask) {
+  return face_lex<int64_t>(x, y, z, nx, ny, nz, mask);
 }
 
 inline int64_t face_lex_count(int nx, int ny, int nz, unsigned mask) {
@@ -107,6 +121,20 @@ inline void fd_tile_grid(int nx, int ny, int nz, bool nt, int& nbx, int& nby, in
   nbz = (nz + zc - 1) / zc;
   ntiles = nbx * nby * ((nbz + zg - 1) / zg * zg);   // whole groups of z-chunks
   per_xcd = (ntiles + N_XCD - 1) / N_XCD;
+}
+
+// Blocks of the four-nodes-per-thread update: FD_THREADS quads of a component's plane, row_zc(nt) planes.
+template <class Args>
+inline void fd_row_grid(Args& a, bool nt) {
+  a.row_q = (a.nx + 3) / 4;
+  a.row_nb = (int)(((int64_t)a.row_q * a.ny + FD_THREADS - 1) / FD_THREADS);
+  a.row_nz = (a.nz + row_zc(nt) - 1) / row_zc(nt);
+  a.row_tiles = 3 * a.row_nb * a.row_nz;
+  const auto inverse = [](int d) { return d > 1 ? (uint32_t)((1ull << 32) / (uint32_t)d) : ~0u; };
+  a.row_q_inv = inverse(a.row_q);
+  a.row_nb_inv = inverse(a.row_nb);
+  a.row_nz_inv = inverse(a.row_nz);
+  a.row_per_xcd = (a.row_tiles + N_XCD - 1) / N_XCD;
 }
 
 // ---- kernel arguments -------------------------------------------------------------------
@@ -156,6 +184,10 @@ struct FdArgs {
   int nx, ny, nz;
   int blo[3], bhi[3];  // FEM box node range [fem_lo, fem_lo + fem_cells] per axis
   int nbx, nby, nbz, ntiles, per_xcd;
+  // four-nodes-per-thread update: quads per row, blocks per plane, z-chunks, blocks and blocks per XCD
+  // (and the divisors' reciprocals)
+  int row_q, row_nb, row_nz, row_tiles, row_per_xcd;
+  uint32_t row_q_inv, row_nb_inv, row_nz_inv;
   float nu2, nu;       // (dt/h)^2, dt/h
   unsigned abs_mask;
   int top_a, top_b;    // top face absorbing at the levels of D+ (a) and D- (b)

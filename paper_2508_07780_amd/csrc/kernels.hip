@@ -322,9 +322,236 @@ __device__ __forceinline__ void fd_tile(const FdArgs& a, const int b) {
   }
 }
 
+// ---------------------------------------------------------------------------------------
+// The same update of one component, four nodes along x per thread (all steps but those with energies and
+// those beside element partitions).  A block takes 256 consecutive quads of the (row, quad of the row) order of a plane, so
+// that rows of any length leave no lane idle but in the last block, and row_zc(NT) planes.  No LDS and no
+// barrier: the neighbours along x are the next lanes' (a wave's end lanes load theirs), the rows above and
+// below are read again (they are in the caches: a block's own rows, or its neighbour's on the same XCD), and all loads of a block are on
+// their way before the first plane is computed.
+// Bound by instructions on grids whose fields the last-level cache holds (about 350 per wave of two planes), by HBM on larger ones.
+// us per forward step, the 32 x 8 tile of one node per thread (bound by its instructions: each node's
+// addresses, LDS accesses and flags) -> this: 117x106x121 17.1 -> 13.8, 128^3 (FEM 32^3) 18.0 -> 14.4, 160^3 32.0 -> 26.6,
+// 192^3 (FEM 96^3) 59.0 -> 51.4, 224^3 88.9 -> 76.7, 288^3 174.8 -> 149.3 (5.8 TB/s by the kernel's minimum).
+// Planes per block, us per step at 128^3 / 160^3: 1 16.5 / 31.2, 2 15.0 / 27.4, 3 16.0 / 28.2, 4 (one loaded ahead: all would be
+// too many registers) 15.8 / 27.9; streaming, at 224^3 / 288^3: 2 80.2 / 152, 3 77.1 / 149, 4 78.9 / 155, 8 80.3 / 159.  All three
+// components in a block, to share the addresses: the compiler keeps all of it in registers (170 to 260).
+// Outer faces: a missing neighbour reads as the node itself (a difference of 0), the other side's counts twice.
+// Quads that reach past the row's end read the next row's values there (the arrays are padded by a quad)
+// and discard them.  Nodes with damping, forcing or a cotangent are done again one by one.
+// ---------------------------------------------------------------------------------------
+typedef float Quad __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ Quad ld_quad(const char* base, uint32_t off) {
+  return *reinterpret_cast<const Quad*>(base + off);
+}
+template <bool NT>
+__device__ __forceinline__ Quad ld_own_quad(const char* base, uint32_t off) {
+  if (NT) return __builtin_nontemporal_load(reinterpret_cast<const Quad*>(base + off));
+  return *reinterpret_cast<const Quad*>(base + off);
+}
+template <bool NT>
+__device__ __forceinline__ void st_own_quad(char* base, uint32_t off, Quad v) {
+  if (NT) __builtin_nontemporal_store(v, reinterpret_cast<Quad*>(base + off));
+  else *reinterpret_cast<Quad*>(base + off) = v;
+}
+// the value of the lane before / after this one; the wave's first / last lane keeps `end`
+__device__ __forceinline__ float lane_before(float v, float end) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(end), __float_as_int(v), 0x138, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float lane_after(float v, float end) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(end), __float_as_int(v), 0x130, 0xf, 0xf, false));
+}
+
+// n / d with inv = floor(2^32 / d), d > 1 (d = 1: 2^32 - 1): at most one too few before the correction
+__device__ __forceinline__ int divide(int n, int d, uint32_t inv) {
+  const int q = (int)__umulhi((uint32_t)n, inv);
+  return n - q * d >= d ? q + 1 : q;
+}
+
+// ADJ: cotangents instead of forcing and traces.
+template <bool ADJ, bool NT, bool OBL = false>
+__device__ __forceinline__ void fd_rows(const FdArgs& a, const int b) {
+#pragma clang fp contract(off)
+  constexpr int ZC = row_zc(NT);
+  const int kx = a.rev ? a.row_per_xcd - 1 - b / N_XCD : b / N_XCD;
+  const int t = (b % N_XCD) * a.row_per_xcd + kx;
+  if (t >= a.row_tiles) return;
+  const int nx = a.nx, ny = a.ny, nz = a.nz, nq = a.row_q;
+  const int r = divide(t, a.row_nb, a.row_nb_inv), yb = t - r * a.row_nb;
+  const int c = divide(r, a.row_nz, a.row_nz_inv), bz = r - c * a.row_nz;
+  const int z0 = bz * ZC, z1 = min(z0 + ZC, nz);
+  const int quads = nq * ny;
+  int qd = yb * FD_THREADS + (int)threadIdx.x;
+  const bool in = qd < quads;
+  if (!in) qd = quads - 1;
+  const int y = divide(qd, nq, a.row_q_inv), q = qd - y * nq, x = 4 * q;
+  const int el = (nx - 1) & 3;                     // the row's last element in its quad
+  const bool row_begin = q == 0, row_end = q == nq - 1;
+  // elements of the quad: on the grid, and of those outside the open box in (x, y)
+  const unsigned on = !in ? 0u : row_end ? (2u << el) - 1u : 15u;
+  const bool y_box = y > a.blo[1] && y < a.bhi[1];
+  unsigned free_xy = on;
+  if (y_box)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (x + e > a.blo[0] && x + e < a.bhi[0]) free_xy &= ~(1u << e);
+  // nothing to update here, nor in the lanes on either side next to this quad
+  const bool idle = !in || (z0 > a.blo[2] && z1 - 1 < a.bhi[2] && y_box && x - 1 > a.blo[0] && x + 4 < a.bhi[0]);
+  if (__builtin_amdgcn_ballot_w64(!idle) == 0) return;
+  const uint32_t plane4 = 4u * (uint32_t)(nx * ny), row4 = 4u * (uint32_t)nx;
+  const uint32_t col4 = 4u * (uint32_t)(y * nx + x);
+  const uint32_t up4 = y > 0 ? col4 - row4 : col4, dn4 = y < ny - 1 ? col4 + row4 : col4;
+  const int lane = threadIdx.x & 63;
+  const bool has_end = (lane == 0 && !row_begin) || (lane == 63 && !row_end);
+  const uint32_t end4 = lane == 0 ? col4 - 4u : col4 + 16u;
+  const size_t comp = (size_t)c * a.N * 4;
+  const char* X = reinterpret_cast<const char*>(a.X_in) + comp;
+  char* P = reinterpret_cast<char*>(a.X_out) + comp;
+  const char* V = a.X_prev ? reinterpret_cast<const char*>(a.X_prev) + comp : P;
+
+  Quad C[ZC + 2], U[ZC], D[ZC], W[ZC];
+  float E[ZC];
+  // Plane z0 + k of the rows beside and of the previous level, the plane above it of this row.  Past the grid the last
+  // plane again, read, not copied: a copy would wait for its load before the others are on their way.
+  const auto load = [&](int k) {
+    const uint32_t zo = (uint32_t)min(z0 + k, nz - 1) * plane4, za = (uint32_t)min(z0 + k + 1, nz - 1) * plane4;
+    C[k + 2] = ld_quad(X, za + col4);
+    U[k] = ld_quad(X, zo + up4);
+    D[k] = ld_quad(X, zo + dn4);
+    W[k] = ld_own_quad<NT>(V, zo + col4);
+    if (has_end) E[k] = ld_at(X, zo + end4);
+  };
+  if (!idle) {
+    C[0] = ld_quad(X, (uint32_t)max(z0 - 1, 0) * plane4 + col4);
+    C[1] = ld_quad(X, (uint32_t)z0 * plane4 + col4);
+#pragma unroll
+    for (int k = 0; k < ZC; ++k) load(k);
+  }
+  // nodes with something of their own: damped or detecting side faces (elements `own`), the planes z = 0 and nz - 1,
+  // the dipole
+  const unsigned sides = (a.abs_mask | a.det_mask) & (DD_FACE_XMIN | DD_FACE_XMAX | DD_FACE_YMIN | DD_FACE_YMAX);
+  const unsigned x_ends = (row_begin ? 1u : 0u) | (row_end ? 1u << el : 0u);
+  const bool y_end = y == 0 || y == ny - 1;
+  const unsigned own = sides ? (y_end ? on : x_ends & on) : 0u;
+  const int dip_z = !ADJ && a.dip_idx >= 0 ? (int)(a.dip_idx / ((int64_t)nx * ny)) : -1;
+  const bool l0_xy = a.iface_out && y >= a.blo[1] && y <= a.bhi[1] && x + 3 >= a.blo[0] && x <= a.bhi[0];
+  const float wy = y_end ? 2.f : 1.f;
+  // While the loads are on their way: the planes' detectors (index of element 0; of element e, e further), and an
+  // adjoint's cotangents of the top plane
+  const unsigned det_mask = ADJ || a.tr_out ? a.det_mask : 0u;
+  const unsigned det_ends =
+      (row_begin && (det_mask & DD_FACE_XMIN) ? 1u : 0u) | (row_end && (det_mask & DD_FACE_XMAX) ? 1u << el : 0u);
+  const bool det_y = (y == 0 && (det_mask & DD_FACE_YMIN)) || (y == ny - 1 && (det_mask & DD_FACE_YMAX));
+  int det0[ZC] = {};
+#pragma unroll
+  for (int k = 0; k < ZC; ++k) {
+    const int z = z0 + k;
+    if (det_mask && (sides || z == 0 || z == nz - 1)) {
+      const bool row = det_y || (z == 0 && (det_mask & DD_FACE_BOTTOM)) || (z == nz - 1 && (det_mask & DD_FACE_TOP));
+      const int e0 = row || (det_ends & 1u) ? 0 : el;
+      det0[k] = face_lex<int>(x + e0, y, z, nx, ny, nz, det_mask) - e0;
+    }
+  }
+  float top_cot[4] = {};
+  if (ADJ && (det_mask & DD_FACE_TOP) && z1 == nz) {
+    const int64_t i = 3ll * (face_lex<int>(0, 0, nz - 1, nx, ny, nz, det_mask) + y * nx + x) + c;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (on >> e & 1) top_cot[e] = a.obs_in ? a.cot_in[i + 3 * e] - a.obs_in[i + 3 * e] : a.cot_in[i + 3 * e];
+  }
+#pragma unroll
+  for (int k = 0; k < ZC; ++k) {
+    const int z = z0 + k;
+    if (z >= z1) break;
+    const Quad &c1 = C[k + 1], &u = U[k], &d = D[k], &p = W[k];
+    const Quad lo = c1 - C[k], hi = c1 - C[k + 2];
+    float left = lane_before(c1[3], E[k]), right = lane_after(c1[0], E[k]);   // (by all lanes)
+    if (row_begin) left = c1[0];
+    Quad xs = c1;                                  // past the row's end: the end's own value
+    if (row_end) {
+      if (el == 0) xs[1] = xs[0];
+      else if (el == 1) xs[2] = xs[1];
+      else if (el == 2) xs[3] = xs[2];
+      else right = xs[3];
+    }
+    const float d01 = xs[0] - xs[1], d12 = xs[1] - xs[2], d23 = xs[2] - xs[3];
+    const float sx[4] = {(xs[0] - left) + d01, d12 - d01, d23 - d12, (xs[3] - right) - d23};
+    const bool z_end = z == 0 || z == nz - 1;
+    const float wz = z_end ? 2.f : 1.f;
+    float S[4];
+    Quad xn;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float wx = x_ends >> e & 1 ? 2.f : 1.f;
+      const float sy = (c1[e] - u[e]) + (c1[e] - d[e]);
+      S[e] = __builtin_fmaf(wz, lo[e] + hi[e], __builtin_fmaf(wy, sy, wx * sx[e]));
+      xn[e] = c1[e] + (__builtin_fmaf(-a.nu2, S[e], c1[e] - p[e]) + 0.f);
+    }
+    const uint32_t zo = (uint32_t)z * plane4;
+    const bool z_box = z > a.blo[2] && z < a.bhi[2];
+    const unsigned m = z_box ? free_xy : on;
+    if (z_end || z == dip_z || sides) {
+      const unsigned mine = m & (z_end ? 15u : z == dip_z ? 15u : own);
+      if (mine) {
+        const bool bzl = z == 0, bzh = z == nz - 1;
+        const unsigned am = a.abs_mask;
+        const int top = (am & DD_FACE_TOP) && bzh;
+        const int fixed = ((am & DD_FACE_BOTTOM) && bzl) + ((am & DD_FACE_YMIN) && y == 0) + ((am & DD_FACE_YMAX) && y == ny - 1);
+        const bool det_row = det_y || (bzl && (det_mask & DD_FACE_BOTTOM)) || (bzh && (det_mask & DD_FACE_TOP));
+        const unsigned det = mine & (det_row ? 15u : det_ends);
+        const int64_t i0 = 3ll * det0[k] + c;
+        const float pw = ADJ || !bzh ? 0.f : c == 0 ? a.pw[0] : c == 1 ? a.pw[1] : a.pw[2];
+        const int64_t dip_e = !ADJ && z == dip_z ? a.dip_idx - (x + (int64_t)nx * (y + (int64_t)ny * z)) : -1;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (!(mine >> e & 1)) continue;
+          const bool bxl = e == 0 && row_begin, bxh = e == el && row_end;
+          float src = 0.f;
+          src += pw;
+          if (!ADJ && OBL && a.pw_kind && bzh)
+            src += (c == 0 ? a.pw_amp[0] : c == 1 ? a.pw_amp[1] : a.pw_amp[2]) * oblique_pulse(a, x + e, y);
+          if (ADJ && (det >> e & 1)) {
+            const int64_t i = i0 + 3 * e;
+            const float r = bzh && (det_mask & DD_FACE_TOP) ? top_cot[e] : a.obs_in ? a.cot_in[i] - a.obs_in[i] : a.cot_in[i];
+            src -= r * (a.dt2_h3 * (float)(1 << ((int)(bxl || bxh) + (int)y_end + (int)z_end)));   // dt^2 / m_i
+          }
+          if (e == dip_e) src += c == 0 ? a.dip[0] : c == 1 ? a.dip[1] : a.dip[2];
+          const int n = fixed + ((am & DD_FACE_XMIN) && bxl) + ((am & DD_FACE_XMAX) && bxh);
+          const int na = n + top * a.top_a, nb = n + top * a.top_b;
+          float out;
+          if (na == 0 && nb == 0) {
+            out = __builtin_fmaf(-a.nu2, S[e], c1[e] - p[e]) + src;
+          } else {
+            const float ba = a.nu * (float)na, bb = a.nu * (float)nb;
+            out = ((1.f - bb) * (c1[e] - p[e]) - a.nu2 * S[e] + src - (ba - bb) * c1[e]) / (1.f + ba);
+          }
+          xn[e] = c1[e] + out;
+          if (!ADJ && (det >> e & 1)) a.tr_out[i0 + 3 * e] = xn[e];
+        }
+      }
+    }
+    if (m == 15u) {
+      st_own_quad<NT>(P, zo + col4, xn);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (m >> e & 1) st_own<NT>(P, zo + col4 + 4 * e, xn[e]);
+    }
+    if (l0_xy && z >= a.blo[2] && z <= a.bhi[2]) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if ((m >> e & 1) && x + e >= a.blo[0] && x + e <= a.bhi[0])
+          a.iface_out[c * a.n_l0 + face_lex_index(x + e - a.blo[0], y - a.blo[1], z - a.blo[2], a.fs[0], a.fs[1], a.fs[2],
+                                                  63u)] = xn[e];
+    }
+  }
+}
+
 template <bool ENERGY, bool NT, bool OBL>
 __global__ __launch_bounds__(FD_THREADS) void fd_step_kernel(FdArgs a) {
-  fd_tile<ENERGY, NT, OBL>(a, blockIdx.x);
+  if (ENERGY) fd_tile<ENERGY, NT, OBL>(a, blockIdx.x);
+  else if (!OBL && a.cot_in) fd_rows<true, NT>(a, blockIdx.x);
+  else fd_rows<false, NT, OBL>(a, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -945,12 +1172,16 @@ __global__ __launch_bounds__(FD_THREADS) void step_kernel(FdArgs fa, FemArgs ea,
     if (p < ea.n_part) fem_stencil_part<ADJ, ENERGY>(ea, p);
     return;
   }
-  fd_tile<ENERGY, NT, OBL>(fa, b - fem_blocks);
+  if (ENERGY) fd_tile<ENERGY, NT, OBL>(fa, b - fem_blocks);
+  else fd_rows<ADJ, NT, OBL>(fa, b - fem_blocks);
 }
 
 // The same fused step on a general mesh: the FEM partitions run the element-coloured code
 // (elements read from global memory, so that a block's LDS stays small enough for the
 // finite-difference tiles of the same launch to share the CUs; GATHER: the gather form).
+// The FD tiles keep one node per thread here: a launch's time is its element partitions', beside which the four-node
+// form's blocks, each with the partitions' LDS, were slower (112^3 refined once: 37.0 against 35.8 ms per
+// gradient).
 // Held to 5 waves per SIMD (at most 96 VGPRs): the adjoint's element sums would otherwise take
 // about 105 and leave the FD tiles of the same launch 4 waves.
 template <bool ADJ, bool ENERGY, bool NT, bool OBL, bool GEOM_LDS, bool GATHER>
@@ -1358,7 +1589,7 @@ __global__ __launch_bounds__(FD_THREADS) void step_kernel_pg(FdArgs fa, FemArgs 
     if (b - fem_blocks < pg_tiles(pg.fs)) pg_tile(pg, b - fem_blocks);
     return;
   }
-  fd_tile<false, NT>(fa, b - fem_blocks - pg_blocks);
+  fd_rows<true, NT>(fa, b - fem_blocks - pg_blocks);
 }
 
 // The same step with the FEM rows in the div-div form R2 (about 73 VGPRs, 6 waves per SIMD,
@@ -1378,17 +1609,18 @@ __global__ __launch_bounds__(FD_THREADS) void step_kernel_r2(FdArgs fa, FemArgs 
     if (b - fem_blocks < pg_tiles(pg.fs)) pg_tile(pg, b - fem_blocks);
     return;
   }
-  fd_tile<ENERGY, NT, OBL>(fa, b - fem_blocks - pg_blocks);
+  if (ENERGY) fd_tile<ENERGY, NT, OBL>(fa, b - fem_blocks - pg_blocks);
+  else fd_rows<ADJ, NT, OBL>(fa, b - fem_blocks - pg_blocks);
 }
 
 // One job's adjoint step together with the next FEM-only recompute step of the segment before
 // it (which writes the other window), arguments by value: blocks [0, fem_blocks) the adjoint
 // FEM partitions, [fem_blocks, fem_blocks + rec_blocks) the recompute partitions, the rest the
 // FD tiles.  The same device code as the batched launch of these two items, without the item
-// lookup; held to 6 waves per SIMD like the batched kernel (the union of the forward and
+// lookup; held to 6 waves per SIMD (streaming: 5) like the batched kernel (the union of the forward and
 // adjoint FEM variants).
 template <bool NT>
-__global__ __launch_bounds__(FD_THREADS, 6) void step_rec_kernel(FdArgs fa, FemArgs ea, int fem_blocks, FemArgs er,
+__global__ __launch_bounds__(FD_THREADS, NT ? 5 : 6) void step_rec_kernel(FdArgs fa, FemArgs ea, int fem_blocks, FemArgs er,
                                                                    int rec_blocks) {
   const int b = blockIdx.x;
   if (b < fem_blocks) {
@@ -1401,13 +1633,13 @@ __global__ __launch_bounds__(FD_THREADS, 6) void step_rec_kernel(FdArgs fa, FemA
     if (p < er.n_part) fem_stencil_part<false, false>(er, p);
     return;
   }
-  fd_tile<false, NT>(fa, b - fem_blocks - rec_blocks);
+  fd_rows<true, NT>(fa, b - fem_blocks - rec_blocks);
 }
 
 void launch_step_rec(const FdArgs& fa, const FemArgs& ea, const FemArgs& er, hipStream_t s, bool nt) {
   const int fem_blocks = (ea.n_part + N_XCD - 1) / N_XCD * N_XCD;
   const int rec_blocks = (er.n_part + N_XCD - 1) / N_XCD * N_XCD;
-  const dim3 grid(fem_blocks + rec_blocks + fa.per_xcd * N_XCD);
+  const dim3 grid(fem_blocks + rec_blocks + fa.row_per_xcd * N_XCD);
   const size_t lds = std::max(stencil_lds(ea), stencil_lds(er));   // the items may be of two problems
   if (nt)
     hipLaunchKernelGGL((step_rec_kernel<true>), grid, dim3(FD_THREADS), lds, s, fa, ea, fem_blocks, er, rec_blocks);
@@ -1427,7 +1659,7 @@ void launch_step_rec(const FdArgs& fa, const FemArgs& ea, const FemArgs& er, hip
 // (93 VGPRs, 5 waves per SIMD instead of 6).
 // ---------------------------------------------------------------------------------------
 template <bool NT, bool OBL>
-__global__ __launch_bounds__(FD_THREADS, 6) void batch_step_kernel(const BatchItem* __restrict__ items, BatchBases bb) {
+__global__ __launch_bounds__(FD_THREADS, NT ? 5 : 6) void batch_step_kernel(const BatchItem* __restrict__ items, BatchBases bb) {
   const int b = blockIdx.x;
   // the item whose block range holds b: binary search over the bases in the arguments
   int lo = 0, hi = bb.n - 1;
@@ -1447,7 +1679,9 @@ __global__ __launch_bounds__(FD_THREADS, 6) void batch_step_kernel(const BatchIt
     }
     return;
   }
-  if (local - it.fem_blocks < it.fd_blocks) fd_tile<false, NT, OBL>(it.fa, local - it.fem_blocks);
+  if (local - it.fem_blocks >= it.fd_blocks) return;
+  if (it.kind == 1) fd_rows<true, NT>(it.fa, local - it.fem_blocks);
+  else fd_rows<false, NT, OBL>(it.fa, local - it.fem_blocks);
 }
 
 void launch_batch(const BatchItem* items_dev, const BatchBases& bases, size_t lds, hipStream_t s, bool nt, bool obl) {
@@ -1572,7 +1806,7 @@ static int grid_for(int64_t n, int block = 256, int cap = 4096) {
 
 template <bool NT>
 static void launch_fd_t(const FdArgs& a, hipStream_t s, bool energy) {
-  const int grid = a.per_xcd * N_XCD;
+  const int grid = (energy ? a.per_xcd : a.row_per_xcd) * N_XCD;
   const bool obl = a.pw_kind != 0;
   if (energy && obl)
     hipLaunchKernelGGL((fd_step_kernel<true, NT, true>), dim3(grid), dim3(FD_THREADS), 0, s, a);
@@ -1686,7 +1920,8 @@ template <bool NT>
 static void launch_step_t(const FdArgs& fa, const FemArgs& ea, hipStream_t s, bool adj, bool energy,
                           const PgArgs* pg) {
   const int fem_blocks = (ea.n_part + N_XCD - 1) / N_XCD * N_XCD;   // keeps FD blocks XCD-aligned
-  const dim3 grid(fem_blocks + fa.per_xcd * N_XCD);
+  const int fd_blocks = (energy ? fa.per_xcd : fa.row_per_xcd) * N_XCD;
+  const dim3 grid(fem_blocks + fd_blocks);
   const size_t lds = stencil_lds_bytes(ea);
   if (ea.r2) {
     PgArgs g{};
@@ -1695,7 +1930,7 @@ static void launch_step_t(const FdArgs& fa, const FemArgs& ea, hipStream_t s, bo
       g = *pg;
       pg_blocks = (pg_tiles(g.fs) + N_XCD - 1) / N_XCD * N_XCD;
     }
-    const dim3 grid_r2(fem_blocks + pg_blocks + fa.per_xcd * N_XCD);
+    const dim3 grid_r2(fem_blocks + pg_blocks + fd_blocks);
     const size_t lds_r2 = pg_blocks ? std::max(lds, PG_LDS_BYTES) : lds;
     if (adj)
       hipLaunchKernelGGL((step_kernel_r2<true, false, NT>), grid_r2, dim3(FD_THREADS), lds_r2, s, fa, ea, fem_blocks, g,
@@ -1714,7 +1949,7 @@ static void launch_step_t(const FdArgs& fa, const FemArgs& ea, hipStream_t s, bo
                          g, 0);
   } else if (adj && pg) {
     const int pg_blocks = (pg_tiles(pg->fs) + N_XCD - 1) / N_XCD * N_XCD;
-    hipLaunchKernelGGL((step_kernel_pg<NT>), dim3(fem_blocks + pg_blocks + fa.per_xcd * N_XCD), dim3(FD_THREADS),
+    hipLaunchKernelGGL((step_kernel_pg<NT>), dim3(fem_blocks + pg_blocks + fd_blocks), dim3(FD_THREADS),
                        std::max(lds, PG_LDS_BYTES), s, fa, ea, fem_blocks, *pg, pg_blocks);
   } else if (adj)
     hipLaunchKernelGGL((step_kernel<true, false, NT>), grid, dim3(FD_THREADS), lds, s, fa, ea, fem_blocks);
@@ -1884,10 +2119,7 @@ __global__ __launch_bounds__(FD_THREADS) void resident_serial_kernel(ResArgs a, 
     __syncthreads();
   };
   auto tiles = [&]() {
-    for (int b = 0; b < fa.per_xcd * N_XCD; ++b) {
-      __syncthreads();
-      fd_tile<false, false, true>(fa, b);
-    }
+    for (int b = 0; b < fa.row_per_xcd * N_XCD; ++b) fd_rows<ADJ, false, !ADJ>(fa, b);
     __syncthreads();
   };
   fa.epart = ea.epart = nullptr;

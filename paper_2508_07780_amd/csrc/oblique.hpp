@@ -14,7 +14,7 @@ namespace dd {
 // A: a kernel's arguments with the wave's pw_* fields.
 template <class A>
 __device__ __forceinline__ float oblique_pulse_at(const A& a, int kind, float tn, int x, int y) {
-  const float tau = a.pw_kx * (float)(x - a.pw_x0) + a.pw_ky * (float)(y - a.pw_y0);
+  const float tau = __builtin_fmaf(a.pw_kx, (float)(x - a.pw_x0), a.pw_ky * (float)(y - a.pw_y0));
   const float u = tn - tau;
   if (kind == DD_SRC_GAUSS_SINE) {
     if (!(fabsf(u) <= a.pw_sup)) return 0.f;
