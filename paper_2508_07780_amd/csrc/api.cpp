@@ -133,7 +133,8 @@ struct dd_problem {
   double* res_tab = nullptr;
   bool res_ready = false;       // the control block has been cleared
   std::vector<int> res_own_api; // what the plans are built from; empty: not eligible
-  StarValues res_star{};
+  bool kuhn = false;            // the assembled stencil is the Kuhn star, of these values
+  StarValues star{};
   int res_mode = -1;            // DD_RESIDENT: 0 off, 1 from the first call on, 2 as 1 but every launch is called off
                                 // (a test of the last resort); else once the plan pays
   std::string err;
@@ -335,6 +336,9 @@ FemArgs fem_base(const dd_problem* p) {
   a.gather = p->fem_gather && p->inc ? 1 : 0;
   a.part_dims = p->part_dims; a.box_codes = p->box_codes; a.slot_off = p->slot_off;
   a.slot_k = p->slot_k; a.slot_b = p->slot_b; a.n_slots = p->n_slots; a.lds_box = p->lds_box;
+  a.kuhn = p->kuhn ? 1 : 0;
+  const StarValues& v = p->star;
+  a.sk1 = v.k1; a.sk6 = v.k6; a.sb1 = v.b1; a.sb2 = v.b2; a.sb4 = v.b4; a.sb6 = v.b6; a.sb12 = v.b12;
   a.n_part = p->n_part;
   a.em1 = p->em1; a.c1 = p->c1; a.c2 = p->c2; a.mass_d = p->mass_d;
   a.n_own = p->n_own; a.n_l0 = p->n_l0; a.N = p->N;
@@ -706,7 +710,7 @@ int res_create(dd_problem* p, bool adj, ResDevice& r, hipStream_t st) {
   if (q.blocks.empty()) return DD_OK;
   r.a.n_blocks = (int)q.blocks.size();
   r.a.n_pub = q.n_pub;
-  const StarValues& v = p->res_star;
+  const StarValues& v = p->star;
   r.a.sk1 = v.k1; r.a.sk6 = v.k6; r.a.sb1 = v.b1; r.a.sb2 = v.b2; r.a.sb4 = v.b4; r.a.sb6 = v.b6; r.a.sb12 = v.b12;
   std::vector<unsigned char> all;
   unsigned char* dev = nullptr;
@@ -1455,8 +1459,9 @@ int create_problem(const dd_problem_desc* desc, const MeshInput* gm, dd_alloc_fn
     chk(upload(p, &p->slot_b, m.slot_b));
   }
   if (const char* e = std::getenv("DD_RESIDENT")) p->res_mode = std::atoi(e);
+  p->kuhn = p->use_stencil && kuhn_star(m, p->star);
   if (p->use_stencil && !p->tb && p->res_mode) {
-    if (kuhn_star(m, p->res_star) && resident_fits(p->d, device_cus())) p->res_own_api.assign(m.own_api.begin(), m.own_api.end());
+    if (p->kuhn && resident_fits(p->d, device_cus())) p->res_own_api.assign(m.own_api.begin(), m.own_api.end());
   }
   chk(dalloc(p, &p->em1, p->n_own));
   chk(dalloc(p, &p->c1, p->n_own));

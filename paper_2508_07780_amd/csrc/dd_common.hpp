@@ -262,6 +262,8 @@ struct FemArgs {
   // assembled-stencil path
   const int* part_dims; const int* box_codes; const int* slot_off; const float* slot_k; const float* slot_b;
   int n_slots, lds_box;
+  int kuhn;            // the stencil is the Kuhn star (kuhn_star), of these values
+  float sk1, sk6, sb1, sb2, sb4, sb6, sb12;
   int n_part;
   int rev;             // 1: each XCD takes its partitions in reverse order (alternate steps)
   int r2;              // div-div form R2 (element mean of eps - 1 outside the divergence)
