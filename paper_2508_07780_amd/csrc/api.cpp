@@ -1214,6 +1214,22 @@ void fem_block(const dd_problem_desc* d, int pb[3]) {
   pb[1] = pb[2] = n8 < 128 ? FEM_PB / 2 : FEM_PB;
 }
 
+// Lattice blocks of a caller's mesh: 8^3 cells, or a quarter of that where those are too few to fill the GPU (a partition
+// keeps one block of threads busy for some 30 us) and the launch's FD tiles take no longer than that (their time
+// then hides the partitions', and the halo nodes that smaller ones repeat cost).  ms per gradient with 8^3 -> 8x4x4:
+// grids of 112^3 and less, FEM 16^3 (8 blocks of 8^3) 6.7 -> 3.9, 32^3 (64) 6.7 -> 4.2, 48^3 (216) 7.5 -> 5.5, 56^3 (343) 9.2
+// -> 7.8; 128^3, 64^3 (512) 5.3 -> 5.2, 72^3 (729) 7.3 -> 8.0; 160^3, 48^3 3.4 -> 3.2, 64^3 3.9 -> 4.3, 96^3 (1728)
+// 10.5 -> 12.5; 192^3, 48^3 3.3 -> 3.5.
+void general_block(const dd_problem_desc* d, int pb[3]) {
+  int64_t n8 = 1, N = 1;
+  for (int a = 0; a < 3; ++a) {
+    n8 *= (d->fem_cells[a] - 1 + FEM_PB - 1) / FEM_PB;
+    N *= d->n_outer[a];
+  }
+  pb[0] = FEM_PB;
+  pb[1] = pb[2] = n8 <= 400 && N <= 5000000 ? FEM_PB / 2 : FEM_PB;
+}
+
 // Incidence lists of the element kernel's gather form: per partition, the elements incident to
 // each owned node in the partition's colour order (its element order), entry i of owned node l
 // at off[p] + i * no + l (element index within the partition << 2 | the node's slot), each list
@@ -1343,7 +1359,7 @@ int create_problem(const dd_problem_desc* desc, const MeshInput* gm, dd_alloc_fn
   HostMesh m;
   int pb[3];
   fem_block(desc, pb);
-  if (gm) pb[0] = pb[1] = pb[2] = FEM_PB;   // a caller mesh: lattice blocks of 8^3 cells by default
+  if (gm) general_block(desc, pb);
   if (const char* e = std::getenv("DD_FEM_PB")) {
     int x = 0, y = 0, z = 0;
     if (std::sscanf(e, "%d,%d,%d", &x, &y, &z) == 3) { pb[0] = x; pb[1] = y; pb[2] = z; }
