@@ -803,10 +803,11 @@ ResArgs res_args(const dd_problem* p, const ResDevice& r) {
 
 // Whether a call of n_src solves runs resident on stream st: with the default launch options, and not within
 // a capture of the caller's (whose replays the ordering of resident launches would not see).  The plan is built when
-// the problem has been asked for 100 + N / 2000 steps: it takes 0.2 ms for 25^3, 1.6 ms for 64^3 and 3.3 ms for 96^3, a step gains 2.5 to 5 us, so a
-// first call that builds it (231 steps of 64^3, 543 of 96^3) costs little more than by launches, and a problem that is solved once
-// for a few steps builds none; a caller that asks for graphs says that the call comes
-// again, and one that has repeated a call that a graph would then hold does so too.
+// the problem has been asked for 100 + N / 1000 steps: it takes 0.2 ms for 25^3, 1.6 ms for 64^3 and 3.5 ms for 96^3, a step
+// then gains 2.5 to 4 us (launches 5.5 / 6.7 / 10.5 us per forward step, resident 2.6 / 4.1 / 7.2), so the plan costs about what
+// its problem's launches have lost by then, and one that is solved for a few steps builds none.  (With a third of the steps the
+// first pass over 74x85x72, two iterations of 89 steps, took 7.2 ms instead of 4.8.)  A caller that asks for graphs says
+// that the call comes again; one that repeats a call is not held up by the first hundred steps.
 bool res_wanted(dd_problem* p, bool adj, int n_src, bool again, hipStream_t st) {
   ResDevice& r = adj ? p->res_adj : p->res_fwd;
   if (p->res_own_api.empty() || !p->res_mode || !p->use_stencil || !p->fused || p->overlap || p->tb || p->r2 || p->init_on ||
@@ -815,7 +816,7 @@ bool res_wanted(dd_problem* p, bool adj, int n_src, bool again, hipStream_t st) 
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
   r.asked = std::min(r.asked + (int64_t)n_src * p->d.n_steps, p->N + 100);
-  if (!r.tried && (p->res_mode > 0 || p->graph == DD_GRAPH_ON || (again && p->N <= kGraphAutoNodes) || 2000 * (r.asked - 100) >= p->N)) {
+  if (!r.tried && (p->res_mode > 0 || p->graph == DD_GRAPH_ON || 1000 * (r.asked - (again ? 0 : 100)) >= p->N)) {
     r.tried = true;
     const std::string err = p->err;
     if (res_create(p, adj, r, st) != DD_OK) {
