@@ -2214,10 +2214,12 @@ __global__ __launch_bounds__(FD_THREADS) void resident_serial_kernel(ResArgs a, 
 }
 
 void launch_resident_serial(const ResArgs& a, const FdArgs& fa, const FemArgs& ea, bool adj, hipStream_t s) {
+  FdArgs f = fa;
+  fd_row_grid(f, false);      // the kernel's z-chunk, whichever one the problem's launches take
   if (adj)
-    hipLaunchKernelGGL((resident_serial_kernel<true>), dim3(1), dim3(FD_THREADS), stencil_lds(ea), s, a, fa, ea);
+    hipLaunchKernelGGL((resident_serial_kernel<true>), dim3(1), dim3(FD_THREADS), stencil_lds(ea), s, a, f, ea);
   else
-    hipLaunchKernelGGL((resident_serial_kernel<false>), dim3(1), dim3(FD_THREADS), stencil_lds(ea), s, a, fa, ea);
+    hipLaunchKernelGGL((resident_serial_kernel<false>), dim3(1), dim3(FD_THREADS), stencil_lds(ea), s, a, f, ea);
 }
 
 }  // namespace dd
