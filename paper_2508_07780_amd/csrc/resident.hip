@@ -263,12 +263,9 @@ __device__ __forceinline__ void fd_brick(const ResArgs& a, const ResBlock& b, fl
   const int t = threadIdx.x, comp = b.comp, nt = a.nt;
   const int SZ = RES_SY * (b.dim[1] + 2);
   // ---- this thread's nodes
-  // (runs are counted from the top: the lowest one may be shorter, and the top plane is every brick's plane b.run - 1
-  // of its last run)
-  const int nxq = (b.dim[0] + 3) / 4, xq = t % nxq, ty = (t / nxq) % b.dim[1], tr = t / (nxq * b.dim[1]);
-  const int runs = (b.dim[2] + b.run - 1) / b.run, z_low = b.dim[2] - (runs - tr) * b.run, z_beg = max(z_low, 0);
-  const int run_ = tr < runs ? z_low + b.run - z_beg : 0;                  // planes of this thread
-  const uint32_t base = 4u + 4u * xq + RES_SY * (ty + 1) + SZ * (z_beg + 1);   // its first row
+  const ResRows rows = res_rows(b.dim, b.run, t);
+  const int xq = rows.xq, ty = rows.ty, z_beg = rows.z, run_ = rows.run;
+  const uint32_t base = rows.base;
   const int gx = b.lo[0] + 4 * xq, gy = b.lo[1] + ty;                    // grid coordinates of its first node
   float wx[4];
 #pragma unroll

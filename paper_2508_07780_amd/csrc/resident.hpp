@@ -60,6 +60,22 @@ struct ResBlock {
   int node_off;                // FEM: first of the brick's entries in fem_node
 };
 
+// The rows of thread t in a finite-difference brick: four nodes along x from 4 xq on of row ty, `run` planes (0: none)
+// from z on; base: LDS float of its first node.  Runs are counted from the top: the lowest one may be shorter, and the
+// top plane is every brick's plane run - 1 of its last run.  Threads without planes read the last run's rows, unused.
+struct ResRows { int xq, ty, z, run; uint32_t base; };
+__host__ __device__ inline ResRows res_rows(const int* dim, int run, int t) {
+  ResRows r;
+  const int nxq = (dim[0] + 3) / 4, tr = t / (nxq * dim[1]), runs = (dim[2] + run - 1) / run;
+  r.xq = t % nxq;
+  r.ty = (t / nxq) % dim[1];
+  const int low = dim[2] - (tr < runs ? runs - tr : 1) * run;
+  r.z = low > 0 ? low : 0;
+  r.run = tr < runs ? low + run - r.z : 0;
+  r.base = (uint32_t)(4 + 4 * r.xq + RES_SY * (r.ty + 1) + RES_SY * (dim[1] + 2) * (r.z + 1));
+  return r;
+}
+
 struct ResCtl {
   unsigned epoch;              // tag of level 0 of the current solve
   int arrive, state, end;      // RES_WAIT .. RES_DONE
