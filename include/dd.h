@@ -373,6 +373,15 @@ int dd_set_graph(dd_problem* p, int32_t mode);
  * DD_GRAPH_ADJOINT (either pointer may be NULL). */
 enum { DD_GRAPH_FORWARD = 0, DD_GRAPH_ADJOINT = 1 };
 int dd_graph_stats(const dd_problem* p, int32_t which, int64_t* captures, int64_t* replays);
+/* Resident solves (all time steps of a source in one launch, on grids that fit on chip), for which =
+ * DD_GRAPH_FORWARD or DD_GRAPH_ADJOINT: solves taken so far, launches called off because their blocks did not all
+ * get a place on the GPU, and solves that another kernel took after that; and the plan in use (all 0: none): blocks,
+ * planes per thread, nodes of the largest finite-element block.  Waits for `stream`. */
+typedef struct dd_resident_info {
+  int64_t solves, called_off, fallback;
+  int32_t blocks, run, fem_nodes;
+} dd_resident_info;
+int dd_resident_stats(dd_problem* p, int32_t which, dd_resident_info* out, void* stream);
 
 /* Div-div form of the FEM rows.  DD_DIVDIV_R1 (default): the nodal product (eps - 1) E inside
  * the element divergence, as eq. forward_prob writes it.  DD_DIVDIV_R2: the element mean of

@@ -754,6 +754,7 @@ int res_create(dd_problem* p, bool adj, ResDevice& r, hipStream_t st) {
   kept.adj = adj;
   kept.rec = rec;
   kept.max_run = q.max_run;
+  kept.max_fem = q.max_fem;
   kept.fem_lds = q.fem_lds;
   kept.fd_cells = q.fd_cells;
   q = std::move(kept);
@@ -1858,6 +1859,25 @@ int dd_graph_stats(const dd_problem* p, int32_t which, int64_t* captures, int64_
   const GraphCache& g = which == DD_GRAPH_FORWARD ? p->gfwd : p->gadj;
   if (captures) *captures = g.captures;
   if (replays) *replays = g.replays;
+  return DD_OK;
+}
+
+int dd_resident_stats(dd_problem* p, int32_t which, dd_resident_info* out, void* stream) {
+  if (!p) return DD_ERR_INVALID_ARG;
+  if (!out || (which != DD_GRAPH_FORWARD && which != DD_GRAPH_ADJOINT)) return fail(p, DD_ERR_INVALID_ARG, "bad argument");
+  const ResDevice& r = which == DD_GRAPH_FORWARD ? p->res_fwd : p->res_adj;
+  *out = dd_resident_info{};
+  if (!r.n_blocks) return DD_OK;
+  out->blocks = r.n_blocks;
+  out->run = r.plan.max_run;
+  out->fem_nodes = r.plan.max_fem;
+  ResCtl c{};
+  if (p->res_ready && (hipMemcpyAsync(&c, p->res_ctl, sizeof(c), hipMemcpyDeviceToHost, (hipStream_t)stream) != hipSuccess ||
+                       hipStreamSynchronize((hipStream_t)stream) != hipSuccess))
+    return fail(p, DD_ERR_HIP, "readback failed");
+  out->solves = c.solves[which];
+  out->called_off = c.called_off[which];
+  out->fallback = c.serial[which];
   return DD_OK;
 }
 

@@ -2099,8 +2099,12 @@ void launch_count_nonfinite(const float* x, int64_t n, int* err, hipStream_t s) 
 template <bool ADJ>
 __global__ __launch_bounds__(FD_THREADS) void resident_serial_kernel(ResArgs a, FdArgs fa, FemArgs ea) {
 #pragma clang fp contract(off)
-  if (a.ctl->state == RES_DONE) return;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, state = a.ctl->state;
+  if (tid == 0) {
+    if (state == RES_DONE) ++a.ctl->solves[ADJ];
+    else ++a.ctl->called_off[ADJ], ++a.ctl->serial[ADJ];
+  }
+  if (state == RES_DONE) return;
   const int64_t n_own = a.n_own, n_l0 = a.n_l0;
   auto zero = [&](float* p, int64_t n) {
     for (int64_t i = tid; i < n; i += FD_THREADS) p[i] = 0.f;
@@ -2210,7 +2214,6 @@ __global__ __launch_bounds__(FD_THREADS) void resident_serial_kernel(ResArgs a, 
       }
     }
   }
-  if (tid == 0) ++a.ctl->serial;
 }
 
 void launch_resident_serial(const ResArgs& a, const FdArgs& fa, const FemArgs& ea, bool adj, hipStream_t s) {

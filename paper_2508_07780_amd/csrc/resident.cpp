@@ -526,6 +526,7 @@ void build(const dd_problem_desc& d, const std::vector<int>& own_api, int cus, b
     const Brick& q = br[b];
     ResBlock& r = bricks[b];
     if (q.fem) {
+      plan.max_fem = std::max(plan.max_fem, q.dim[0] * q.dim[1] * q.dim[2]);
       plan.fem_lds = std::max(plan.fem_lds, fem_bytes(q.dim[0], q.dim[1], q.dim[2], rec));
       plan.blocks.push_back(r);
       continue;

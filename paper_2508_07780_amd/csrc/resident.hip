@@ -944,10 +944,10 @@ __global__ void resident_begin_kernel(ResCtl* c, int tags, double* tab, int off,
   for (int i = threadIdx.x; i < n; i += blockDim.x) tab[off + i] = v.v[i];
 }
 // between two attempts: forget one that was called off
-__global__ void resident_retry_kernel(ResCtl* c) {
+__global__ void resident_retry_kernel(ResCtl* c, int adj) {
   if (c->state == RES_OFF) {
     c->arrive = c->state = c->end = 0;
-    ++c->attempts;
+    ++c->called_off[adj];
   }
 }
 
@@ -955,7 +955,7 @@ template <int RUN, bool ADJ, bool REC>
 void launch_t(const ResArgs& a, size_t lds, hipStream_t s) {
   (void)hipFuncSetAttribute((const void*)resident_kernel<RUN, ADJ, REC>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   for (int i = 0; i < 2; ++i) {
-    if (i) hipLaunchKernelGGL(resident_retry_kernel, dim3(1), dim3(1), 0, s, a.ctl);
+    if (i) hipLaunchKernelGGL(resident_retry_kernel, dim3(1), dim3(1), 0, s, a.ctl, ADJ ? 1 : 0);
     hipLaunchKernelGGL((resident_kernel<RUN, ADJ, REC>), dim3(a.n_blocks), dim3(RES_THREADS), lds, s, a);
   }
 }

@@ -79,7 +79,9 @@ __host__ __device__ inline ResRows res_rows(const int* dim, int run, int t) {
 struct ResCtl {
   unsigned epoch;              // tag of level 0 of the current solve
   int arrive, state, end;      // RES_WAIT .. RES_DONE
-  int attempts, serial;        // attempts called off, solves taken by the one-block kernel
+  // per direction (forward, adjoint): solves taken by the resident kernel, launches called off, solves taken by the
+  // one-block kernel
+  int solves[2], called_off[2], serial[2];
 };
 enum { RES_WAIT = 0, RES_GO = 1, RES_OFF = 2, RES_FAILED = 3, RES_DONE = 4 };
 
@@ -99,6 +101,7 @@ struct ResPlan {
   int n_pub = 0;                       // published nodes
   bool adj = false, rec = false;
   int max_run = 0;                     // planes per thread
+  int max_fem = 0;                     // nodes of the largest FEM brick
   size_t fem_lds = 0;                  // LDS of the largest FEM brick
   int fd_cells = 0;                    // largest FD box (cells)
   size_t lds() const { return fem_lds > 4 * (size_t)fd_cells ? fem_lds : 4 * (size_t)fd_cells; }

@@ -252,6 +252,15 @@ class Problem:
         _lib.check(_lib.load().dd_graph_stats(self._h, code, ctypes.byref(c), ctypes.byref(r)), self._h)
         return c.value, r.value
 
+    def resident_stats(self, which="forward"):
+        """Of the resident solves, "forward" or "adjoint": dict of the solves taken, the launches called off, the
+        solves another kernel took then, and the plan's blocks, planes per thread and finite-element nodes per
+        block (0: no plan)."""
+        info = _lib.ResidentInfo()
+        code = {"forward": 0, "adjoint": 1}[which]
+        _lib.check(_lib.load().dd_resident_stats(self._h, code, ctypes.byref(info), _stream()), self._h)
+        return {name: getattr(info, name) for name, _ in info._fields_}
+
     def check_finite(self):
         """Raise DDError (DD_ERR_UNSTABLE) if the current fields hold non-finite values."""
         _lib.check(_lib.load().dd_check_finite(self._h, _stream()), self._h)

@@ -1,7 +1,8 @@
 """Brick plans of resident solves, checked on the host (tests/native/resident_check.cpp).
 
 * every LDS row that a thread of a finite-difference brick reads lies in its brick's box, for the threads
-  without nodes too.
+  without nodes too;
+* the problems of resident_forms take the kernel variants that they are there for.
 """
 
 import math
@@ -10,6 +11,8 @@ import random
 import subprocess
 
 import pytest
+
+from tests.resident_forms import STEPS, VARIANTS, variant
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2508_07780_amd", "csrc")
@@ -53,3 +56,22 @@ def test_rows_stay_in_the_brick(check):
     assert sum(r[0] > 0 for r in rows) > 200
     for p, r in zip(problems, rows):
         assert r[4] == 0, (p, r)
+
+
+def test_forms_take_every_variant(check):
+    problems = []
+    for n, lo, cells, det, damp, ck, *_ in VARIANTS.values():
+        for adj in (0, 1):
+            problems.append((CUS, *n, *lo, *cells, STEPS, det, damp, adj, adj and ck < STEPS))
+    rows = check(problems)
+    seen = set()
+    for i, (name, form) in enumerate(VARIANTS.items()):
+        for adj in (0, 1):
+            r = rows[2 * i + adj]
+            assert r[0] and variant(r[1], r[2]) == form[7 + adj], (name, adj, r)
+            rec = adj and form[5] < STEPS
+            seen |= {("run", adj, rec, form[7 + adj][0]), ("fem", adj, rec, form[7 + adj][1])}
+    # the adjoint with recompute holds more per node: its cuts have two planes per thread nowhere
+    assert seen >= {("run", 0, 0, k) for k in (2, 4, 8, 12)} | {("run", 1, False, k) for k in (2, 4, 8, 12)}
+    assert seen >= {("run", 1, True, k) for k in (4, 8, 12)}
+    assert seen >= {("fem", a, r, k) for a, r in ((0, 0), (1, False), (1, True)) for k in (1, 2, 3)}
