@@ -57,6 +57,8 @@ struct dd_problem {
   int *part_dims = nullptr, *box_codes = nullptr, *slot_off = nullptr;
   float *slot_k = nullptr, *slot_b = nullptr;
   int nbx = 0, nby = 0, nbz = 0, n_tiles = 0, per_xcd = 0;
+  int rows_mode = -1;     // DD_FD_ROWS: 0 tiles, 1 four nodes per thread; else as it pays (rows_pay)
+  bool long_parts = false;   // FEM partitions of 8^3 nodes
   bool fd_nt = false;     // non-temporal own-node streams in the FD tiles (grid exceeds the LLC)
   // topology (device)
   int *own_off = nullptr, *halo_off = nullptr, *halo = nullptr, *col_base = nullptr, *ncol = nullptr,
@@ -299,6 +301,27 @@ bool top_absorbs(const dd_problem* p, int64_t level) {
   return (p->d.absorbing_faces & DD_FACE_TOP) && (double)level * p->d.dt > p->d.t_switch;
 }
 
+// Whether a step takes four nodes per thread (fd_rows) instead of the tile of one.
+// - Up to three tiles a CU the step is as long as one block, and the nodes with something of their own (damped or
+//   detecting side faces; an adjoint's cotangents) come one after another in a thread of four.  us per step, tile / rows,
+//   forward and adjoint, all faces detecting: 25^3 5.55 / 6.13 and 5.94 / 7.03, 40^3 5.43 / 5.87 and 6.18 / 6.89, 64^3
+//   (512 tiles) 7.20 / 7.64 and 7.85 / 7.97, 150x40x45 (575) 7.12 / 7.79 and 7.70 / 7.97, 66^3 (891) 8.56 / 7.84 and
+//   9.07 / 8.11; only the top detecting: forward 25^3 5.13 / 4.84, 40^3 5.13 / 5.18, 64^3 6.71 / 6.62, adjoint 5.09 / 4.75,
+//   5.40 / 5.78, 6.57 / 6.60; with the paper-formula gradient 5.31 / 4.89 and, 64^3, 8.00 / 7.50.
+// - The form R2's partitions of 8^3 nodes take 14 us each, more beside the rows' blocks than beside the tiles', which
+//   counts where the launch ends with them: 96^3 with 48^3 15.5 / 16.0 and 18.5 / 19.6, 112^3 16.3 / 17.5 and 20.6 / 21.0,
+//   120^3 17.5 / 18.1 and 21.6 / 21.6, 128^3 18.8 / 18.5 and 22.6 / 22.1; with 64^3, 96^3 17.4 / 18.0 and 23.8 / 23.5,
+//   112^3 20.9 / 18.5 and 29.4 / 25.3; with 40^3 (blocks of 8x4x4), 80^3 11.0 / 10.3 and 12.6 / 12.5.
+constexpr int64_t kTilesFew = 768;
+bool rows_pay(const dd_problem* p, bool adj) {
+  if (p->rows_mode >= 0) return p->rows_mode != 0;
+  constexpr unsigned sides = DD_FACE_XMIN | DD_FACE_XMAX | DD_FACE_YMIN | DD_FACE_YMAX;
+  const bool own = ((p->d.absorbing_faces | p->d.detector_faces) & sides) || (adj && !p->pg_on);
+  if (own && p->n_tiles <= kTilesFew) return false;
+  if (p->r2 && p->long_parts && (p->N <= 1000000 || (p->n_part <= 256 && p->N <= 1900000))) return false;
+  return true;
+}
+
 FdArgs fd_base(const dd_problem* p) {
   FdArgs a;
   std::memset(&a, 0, sizeof(a));
@@ -311,6 +334,7 @@ FdArgs fd_base(const dd_problem* p) {
   }
   a.nbx = p->nbx; a.nby = p->nby; a.nbz = p->nbz; a.ntiles = p->n_tiles; a.per_xcd = p->per_xcd;
   fd_row_grid(a, p->fd_nt);
+  a.rows = rows_pay(p, false) ? 1 : 0;
   const double nu = p->d.dt / p->d.h;
   a.nu = (float)nu;
   a.nu2 = (float)(nu * nu);
@@ -584,6 +608,7 @@ void adj_step_args(const dd_problem* p, int s, int64_t k, int64_t k0, const floa
   fa.top_b = top_absorbs(p, k + 1) ? 1 : 0;
   for (int c = 0; c < 3; ++c) fa.pw[c] = fa.dip[c] = 0.f;
   fa.dip_idx = -1;
+  fa.rows = rows_pay(p, true) ? 1 : 0;
   fa.tr_out = nullptr;
   const int64_t row = ((int64_t)s * nt + (k - 1)) * p->n_det * 3;
   fa.cot_in = cot + row;
@@ -1379,6 +1404,7 @@ int create_problem(const dd_problem_desc* desc, const MeshInput* gm, dd_alloc_fn
   }
   p->general = gm != nullptr;
   p->n_extra = gm ? gm->n_extra : 0;
+  p->long_parts = pb[0] * pb[1] * pb[2] >= FEM_PB * FEM_PB * FEM_PB;
   p->n_fem = m.n_fem;
   p->n_own = m.n_own;
   p->n_l0 = m.n_l0;
@@ -1396,6 +1422,7 @@ int create_problem(const dd_problem_desc* desc, const MeshInput* gm, dd_alloc_fn
   }
   p->fd_nt = fd_field_bytes(p) > LLC_BYTES;
   if (const char* e = std::getenv("DD_FD_NT")) p->fd_nt = std::atoi(e) != 0;
+  if (const char* e = std::getenv("DD_FD_ROWS")) p->rows_mode = std::atoi(e) != 0 ? 1 : 0;
   fd_tile_grid(p->nx, p->ny, p->nz, p->fd_nt, p->nbx, p->nby, p->nbz, p->n_tiles, p->per_xcd);
   // temporal blocking (two-step launches), an option of the fused single-stream stencil path:
   // DD_TB=1 switches it on
@@ -2515,7 +2542,7 @@ int dd_batch_step(dd_batch* b, int32_t max_steps, void* stream) {
     }
     BatchBases bases[dd_batch::seg];
     size_t lds[dd_batch::seg];
-    bool nt[dd_batch::seg], obl[dd_batch::seg];
+    bool nt[dd_batch::seg], obl[dd_batch::seg], rows[dd_batch::seg];
     int m = 0;
     bool finished = false;
     while (m < b->seg && iter < max_steps && !b->jobs.empty()) {
@@ -2538,7 +2565,16 @@ int dd_batch_step(dd_batch* b, int32_t max_steps, void* stream) {
       // each item's tile grid is laid out for that chunk
       const bool use_nt = b->nt_mode < 0 ? fd_bytes > LLC_BYTES : b->nt_mode != 0;
       bool use_obl = false;
-      for (int i = 0; i < n; ++i) use_obl |= h[i].fa.pw_kind != 0;
+      // the tiles where every item's grid prefers them and they are few together (rows_pay)
+      bool use_rows = use_nt;
+      int64_t tiles = 0;
+      for (int i = 0; i < n; ++i) {
+        use_obl |= h[i].fa.pw_kind != 0;
+        if (h[i].kind == 2) continue;
+        use_rows |= h[i].fa.rows != 0;
+        tiles += h[i].fa.ntiles;
+      }
+      if (n > 1 && tiles > kTilesFew) use_rows = true;
       for (int i = 0; i < n; ++i) {
         BatchItem& it = h[i];
         const dd_problem* q = owner[i];
@@ -2547,7 +2583,7 @@ int dd_batch_step(dd_batch* b, int32_t max_steps, void* stream) {
         if (it.kind != 2) {
           fd_tile_grid(q->nx, q->ny, q->nz, use_nt, it.fa.nbx, it.fa.nby, it.fa.nbz, it.fa.ntiles, it.fa.per_xcd);
           fd_row_grid(it.fa, use_nt);
-          it.fd_blocks = it.fa.row_per_xcd * N_XCD;
+          it.fd_blocks = (use_rows ? it.fa.row_per_xcd : it.fa.per_xcd) * N_XCD;
         }
         l = std::max(l, stencil_lds(it.ea));
         bases[m].base[i] = base;   // each item's FEM partitions, then its FD tiles
@@ -2558,6 +2594,7 @@ int dd_batch_step(dd_batch* b, int32_t max_steps, void* stream) {
       lds[m] = l;
       nt[m] = use_nt;
       obl[m] = use_obl;
+      rows[m] = use_rows;
       ++m;
       ++iter;
       if (std::any_of(b->jobs.begin(), b->jobs.end(), [](const BatchJob& j) { return j.phase == 2; })) {
@@ -2598,7 +2635,7 @@ int dd_batch_step(dd_batch* b, int32_t max_steps, void* stream) {
           // one job's adjoint step and its recompute step: likewise by value
           launch_step_rec(one.fa, one.ea, two.ea, st, nt[k]);
         else
-          launch_batch(b->dev + off + (size_t)k * b->width, bases[k], lds[k], st, nt[k], obl[k]);
+          launch_batch(b->dev + off + (size_t)k * b->width, bases[k], lds[k], st, nt[k], obl[k], rows[k]);
       }
       if (upload && hipEventRecord(b->ev_used[g], st) != hipSuccess) {
         b->err = "batch event record failed";

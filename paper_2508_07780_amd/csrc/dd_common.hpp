@@ -186,6 +186,7 @@ struct FdArgs {
   int nbx, nby, nbz, ntiles, per_xcd;
   // four-nodes-per-thread update: quads per row, blocks per plane, z-chunks, blocks and blocks per XCD
   // (and the divisors' reciprocals)
+  int rows;            // 1: that update, 0: the tile (streaming launches take the rows in any case)
   int row_q, row_nb, row_nz, row_tiles, row_per_xcd;
   uint32_t row_q_inv, row_nb_inv, row_nz_inv;
   float nu2, nu;       // (dt/h)^2, dt/h
@@ -319,7 +320,8 @@ struct BatchBases {
   int base[BATCH_MAX + 1];
 };
 // obl: some item carries an obliquely incident plane wave (pw_kind != 0)
-void launch_batch(const BatchItem* items_dev, const BatchBases& bases, size_t lds, hipStream_t s, bool nt, bool obl);
+void launch_batch(const BatchItem* items_dev, const BatchBases& bases, size_t lds, hipStream_t s, bool nt, bool obl,
+                  bool rows);
 size_t stencil_lds(const FemArgs& a);
 void launch_energy_reduce(const double* part, int n, double* out, hipStream_t s);
 void launch_fill_f32(float* p, int64_t n, float v, hipStream_t s);

@@ -548,9 +548,16 @@ __device__ __forceinline__ void fd_rows(const FdArgs& a, const int b) {
   }
 }
 
-template <bool ENERGY, bool NT, bool OBL>
+// The finite-difference update of a step's block b: ROWS, four nodes per thread (fd_rows), else the tile.
+template <bool ADJ, bool ENERGY, bool NT, bool OBL, bool ROWS>
+__device__ __forceinline__ void fd_block(const FdArgs& a, const int b) {
+  if (ENERGY || !ROWS) fd_tile<ENERGY, NT, OBL>(a, b);
+  else fd_rows<ADJ, NT, OBL>(a, b);
+}
+
+template <bool ENERGY, bool NT, bool OBL, bool ROWS = true>
 __global__ __launch_bounds__(FD_THREADS) void fd_step_kernel(FdArgs a) {
-  if (ENERGY) fd_tile<ENERGY, NT, OBL>(a, blockIdx.x);
+  if (ENERGY || !ROWS) fd_tile<ENERGY, NT, OBL>(a, blockIdx.x);
   else if (!OBL && a.cot_in) fd_rows<true, NT>(a, blockIdx.x);
   else fd_rows<false, NT, OBL>(a, blockIdx.x);
 }
@@ -1170,7 +1177,7 @@ __global__ __launch_bounds__(STENCIL_THREADS) void fem_stencil_kernel(FemArgs a)
 // One launch per time step: blocks [0, fem_blocks) advance the FEM partitions (scheduled
 // first: their staging is latency-bound), the remaining blocks the finite-difference
 // tiles.  Both read level n and write level n+1 only, so they need no ordering.
-template <bool ADJ, bool ENERGY, bool NT, bool OBL = false>
+template <bool ADJ, bool ENERGY, bool NT, bool OBL = false, bool ROWS = true>
 __global__ __launch_bounds__(FD_THREADS) void step_kernel(FdArgs fa, FemArgs ea, int fem_blocks) {
   const int b = blockIdx.x;
   if (b < fem_blocks) {
@@ -1178,8 +1185,7 @@ __global__ __launch_bounds__(FD_THREADS) void step_kernel(FdArgs fa, FemArgs ea,
     if (p < ea.n_part) fem_stencil_part<ADJ, ENERGY>(ea, p);
     return;
   }
-  if (ENERGY) fd_tile<ENERGY, NT, OBL>(fa, b - fem_blocks);
-  else fd_rows<ADJ, NT, OBL>(fa, b - fem_blocks);
+  fd_block<ADJ, ENERGY, NT, OBL, ROWS>(fa, b - fem_blocks);
 }
 
 // The same fused step on a general mesh: the FEM partitions run the element-coloured code
@@ -1582,7 +1588,7 @@ __global__ __launch_bounds__(FD_THREADS) void step_pair_kernel(FdArgs fa, FemArg
 // The adjoint step of the form R1 with the paper-formula variant on: it also carries the
 // variant's div-div gradient terms of its input level (blocks [fem_blocks, fem_blocks +
 // pg_blocks), pg_tile), which read lambda^k and the saved E^k that the step does not write.
-template <bool NT>
+template <bool NT, bool ROWS = true>
 __global__ __launch_bounds__(FD_THREADS) void step_kernel_pg(FdArgs fa, FemArgs ea, int fem_blocks, PgArgs pg,
                                                              int pg_blocks) {
   const int b = blockIdx.x;
@@ -1595,14 +1601,14 @@ __global__ __launch_bounds__(FD_THREADS) void step_kernel_pg(FdArgs fa, FemArgs 
     if (b - fem_blocks < pg_tiles(pg.fs)) pg_tile(pg, b - fem_blocks);
     return;
   }
-  fd_rows<true, NT>(fa, b - fem_blocks - pg_blocks);
+  fd_block<true, false, NT, false, ROWS>(fa, b - fem_blocks - pg_blocks);
 }
 
 // The same step with the FEM rows in the div-div form R2 (about 73 VGPRs, 6 waves per SIMD,
 // with r2_term's cell loop unrolled four at a time).  An adjoint step also carries the
 // div-div gradient terms of its input level (blocks [fem_blocks, fem_blocks + pg_blocks),
 // pg_tile): they read lambda^k and the saved E^k, which the step does not write.
-template <bool ADJ, bool ENERGY, bool NT, bool OBL = false>
+template <bool ADJ, bool ENERGY, bool NT, bool OBL = false, bool ROWS = true>
 __global__ __launch_bounds__(FD_THREADS) void step_kernel_r2(FdArgs fa, FemArgs ea, int fem_blocks, PgArgs pg,
                                                                   int pg_blocks) {
   const int b = blockIdx.x;
@@ -1615,8 +1621,7 @@ __global__ __launch_bounds__(FD_THREADS) void step_kernel_r2(FdArgs fa, FemArgs 
     if (b - fem_blocks < pg_tiles(pg.fs)) pg_tile(pg, b - fem_blocks);
     return;
   }
-  if (ENERGY) fd_tile<ENERGY, NT, OBL>(fa, b - fem_blocks - pg_blocks);
-  else fd_rows<ADJ, NT, OBL>(fa, b - fem_blocks - pg_blocks);
+  fd_block<ADJ, ENERGY, NT, OBL, ROWS>(fa, b - fem_blocks - pg_blocks);
 }
 
 // One job's adjoint step together with the next FEM-only recompute step of the segment before
@@ -1625,7 +1630,7 @@ __global__ __launch_bounds__(FD_THREADS) void step_kernel_r2(FdArgs fa, FemArgs 
 // FD tiles.  The same device code as the batched launch of these two items, without the item
 // lookup; held to 6 waves per SIMD (streaming: 5) like the batched kernel (the union of the forward and
 // adjoint FEM variants).
-template <bool NT>
+template <bool NT, bool ROWS = true>
 __global__ __launch_bounds__(FD_THREADS, NT ? 5 : 6) void step_rec_kernel(FdArgs fa, FemArgs ea, int fem_blocks, FemArgs er,
                                                                    int rec_blocks) {
   const int b = blockIdx.x;
@@ -1639,16 +1644,19 @@ __global__ __launch_bounds__(FD_THREADS, NT ? 5 : 6) void step_rec_kernel(FdArgs
     if (p < er.n_part) fem_stencil_part<false, false>(er, p);
     return;
   }
-  fd_rows<true, NT>(fa, b - fem_blocks - rec_blocks);
+  fd_block<true, false, NT, false, ROWS>(fa, b - fem_blocks - rec_blocks);
 }
 
 void launch_step_rec(const FdArgs& fa, const FemArgs& ea, const FemArgs& er, hipStream_t s, bool nt) {
   const int fem_blocks = (ea.n_part + N_XCD - 1) / N_XCD * N_XCD;
   const int rec_blocks = (er.n_part + N_XCD - 1) / N_XCD * N_XCD;
-  const dim3 grid(fem_blocks + rec_blocks + fa.row_per_xcd * N_XCD);
+  const bool rows = nt || fa.rows;
+  const dim3 grid(fem_blocks + rec_blocks + (rows ? fa.row_per_xcd : fa.per_xcd) * N_XCD);
   const size_t lds = std::max(stencil_lds(ea), stencil_lds(er));   // the items may be of two problems
   if (nt)
     hipLaunchKernelGGL((step_rec_kernel<true>), grid, dim3(FD_THREADS), lds, s, fa, ea, fem_blocks, er, rec_blocks);
+  else if (!rows)
+    hipLaunchKernelGGL((step_rec_kernel<false, false>), grid, dim3(FD_THREADS), lds, s, fa, ea, fem_blocks, er, rec_blocks);
   else
     hipLaunchKernelGGL((step_rec_kernel<false>), grid, dim3(FD_THREADS), lds, s, fa, ea, fem_blocks, er, rec_blocks);
 }
@@ -1664,7 +1672,7 @@ void launch_step_rec(const FdArgs& fa, const FemArgs& ea, const FemArgs& er, hip
 // kernel; without the occupancy bound the compiler allocates registers for their union
 // (93 VGPRs, 5 waves per SIMD instead of 6).
 // ---------------------------------------------------------------------------------------
-template <bool NT, bool OBL>
+template <bool NT, bool OBL, bool ROWS = true>
 __global__ __launch_bounds__(FD_THREADS, NT ? 5 : 6) void batch_step_kernel(const BatchItem* __restrict__ items, BatchBases bb) {
   const int b = blockIdx.x;
   // the item whose block range holds b: binary search over the bases in the arguments
@@ -1686,20 +1694,26 @@ __global__ __launch_bounds__(FD_THREADS, NT ? 5 : 6) void batch_step_kernel(cons
     return;
   }
   if (local - it.fem_blocks >= it.fd_blocks) return;
-  if (it.kind == 1) fd_rows<true, NT>(it.fa, local - it.fem_blocks);
+  if (!ROWS) fd_tile<false, NT, OBL>(it.fa, local - it.fem_blocks);
+  else if (it.kind == 1) fd_rows<true, NT>(it.fa, local - it.fem_blocks);
   else fd_rows<false, NT, OBL>(it.fa, local - it.fem_blocks);
 }
 
-void launch_batch(const BatchItem* items_dev, const BatchBases& bases, size_t lds, hipStream_t s, bool nt, bool obl) {
+void launch_batch(const BatchItem* items_dev, const BatchBases& bases, size_t lds, hipStream_t s, bool nt, bool obl,
+                  bool rows) {
   const dim3 grid(bases.base[bases.n]);
   if (nt && obl)
     hipLaunchKernelGGL((batch_step_kernel<true, true>), grid, dim3(FD_THREADS), lds, s, items_dev, bases);
   else if (nt)
     hipLaunchKernelGGL((batch_step_kernel<true, false>), grid, dim3(FD_THREADS), lds, s, items_dev, bases);
+  else if (!rows && obl)
+    hipLaunchKernelGGL((batch_step_kernel<false, true, false>), grid, dim3(FD_THREADS), lds, s, items_dev, bases);
+  else if (!rows)
+    hipLaunchKernelGGL((batch_step_kernel<false, false, false>), grid, dim3(FD_THREADS), lds, s, items_dev, bases);
   else if (obl)
-    hipLaunchKernelGGL((batch_step_kernel<false, true>), grid, dim3(FD_THREADS), lds, s, items_dev, bases);
+    hipLaunchKernelGGL((batch_step_kernel<false, true, true>), grid, dim3(FD_THREADS), lds, s, items_dev, bases);
   else
-    hipLaunchKernelGGL((batch_step_kernel<false, false>), grid, dim3(FD_THREADS), lds, s, items_dev, bases);
+    hipLaunchKernelGGL((batch_step_kernel<false, false, true>), grid, dim3(FD_THREADS), lds, s, items_dev, bases);
 }
 
 size_t stencil_lds(const FemArgs& a) {
@@ -1810,14 +1824,24 @@ static int grid_for(int64_t n, int block = 256, int cap = 4096) {
   return (int)g;
 }
 
+static void launch_fd_tiles(const FdArgs& a, int grid, hipStream_t s) {
+  if (a.pw_kind)
+    hipLaunchKernelGGL((fd_step_kernel<false, false, true, false>), dim3(grid), dim3(FD_THREADS), 0, s, a);
+  else
+    hipLaunchKernelGGL((fd_step_kernel<false, false, false, false>), dim3(grid), dim3(FD_THREADS), 0, s, a);
+}
+
 template <bool NT>
 static void launch_fd_t(const FdArgs& a, hipStream_t s, bool energy) {
-  const int grid = (energy ? a.per_xcd : a.row_per_xcd) * N_XCD;
+  const bool rows = NT || a.rows;
+  const int grid = (energy || !rows ? a.per_xcd : a.row_per_xcd) * N_XCD;
   const bool obl = a.pw_kind != 0;
   if (energy && obl)
     hipLaunchKernelGGL((fd_step_kernel<true, NT, true>), dim3(grid), dim3(FD_THREADS), 0, s, a);
   else if (energy)
     hipLaunchKernelGGL((fd_step_kernel<true, NT, false>), dim3(grid), dim3(FD_THREADS), 0, s, a);
+  else if (!rows)
+    launch_fd_tiles(a, grid, s);
   else if (obl)
     hipLaunchKernelGGL((fd_step_kernel<false, NT, true>), dim3(grid), dim3(FD_THREADS), 0, s, a);
   else
@@ -1922,11 +1946,11 @@ void launch_fem_stencil_adj(const FemArgs& a, int n_part, hipStream_t s) {
                        stencil_lds_bytes(a), s, a);
 }
 
-template <bool NT>
+template <bool NT, bool ROWS>
 static void launch_step_t(const FdArgs& fa, const FemArgs& ea, hipStream_t s, bool adj, bool energy,
                           const PgArgs* pg) {
   const int fem_blocks = (ea.n_part + N_XCD - 1) / N_XCD * N_XCD;   // keeps FD blocks XCD-aligned
-  const int fd_blocks = (energy ? fa.per_xcd : fa.row_per_xcd) * N_XCD;
+  const int fd_blocks = (energy || !ROWS ? fa.per_xcd : fa.row_per_xcd) * N_XCD;
   const dim3 grid(fem_blocks + fd_blocks);
   const size_t lds = stencil_lds_bytes(ea);
   if (ea.r2) {
@@ -1939,34 +1963,34 @@ static void launch_step_t(const FdArgs& fa, const FemArgs& ea, hipStream_t s, bo
     const dim3 grid_r2(fem_blocks + pg_blocks + fd_blocks);
     const size_t lds_r2 = pg_blocks ? std::max(lds, PG_LDS_BYTES) : lds;
     if (adj)
-      hipLaunchKernelGGL((step_kernel_r2<true, false, NT>), grid_r2, dim3(FD_THREADS), lds_r2, s, fa, ea, fem_blocks, g,
+      hipLaunchKernelGGL((step_kernel_r2<true, false, NT, false, ROWS>), grid_r2, dim3(FD_THREADS), lds_r2, s, fa, ea, fem_blocks, g,
                          pg_blocks);
     else if (fa.pw_kind && energy)
       hipLaunchKernelGGL((step_kernel_r2<false, true, NT, true>), grid_r2, dim3(FD_THREADS), lds_r2, s, fa, ea,
                          fem_blocks, g, 0);
     else if (fa.pw_kind)
-      hipLaunchKernelGGL((step_kernel_r2<false, false, NT, true>), grid_r2, dim3(FD_THREADS), lds_r2, s, fa, ea,
+      hipLaunchKernelGGL((step_kernel_r2<false, false, NT, true, ROWS>), grid_r2, dim3(FD_THREADS), lds_r2, s, fa, ea,
                          fem_blocks, g, 0);
     else if (energy)
       hipLaunchKernelGGL((step_kernel_r2<false, true, NT>), grid_r2, dim3(FD_THREADS), lds_r2, s, fa, ea, fem_blocks,
                          g, 0);
     else
-      hipLaunchKernelGGL((step_kernel_r2<false, false, NT>), grid_r2, dim3(FD_THREADS), lds_r2, s, fa, ea, fem_blocks,
+      hipLaunchKernelGGL((step_kernel_r2<false, false, NT, false, ROWS>), grid_r2, dim3(FD_THREADS), lds_r2, s, fa, ea, fem_blocks,
                          g, 0);
   } else if (adj && pg) {
     const int pg_blocks = (pg_tiles(pg->fs) + N_XCD - 1) / N_XCD * N_XCD;
-    hipLaunchKernelGGL((step_kernel_pg<NT>), dim3(fem_blocks + pg_blocks + fd_blocks), dim3(FD_THREADS),
+    hipLaunchKernelGGL((step_kernel_pg<NT, ROWS>), dim3(fem_blocks + pg_blocks + fd_blocks), dim3(FD_THREADS),
                        std::max(lds, PG_LDS_BYTES), s, fa, ea, fem_blocks, *pg, pg_blocks);
   } else if (adj)
-    hipLaunchKernelGGL((step_kernel<true, false, NT>), grid, dim3(FD_THREADS), lds, s, fa, ea, fem_blocks);
+    hipLaunchKernelGGL((step_kernel<true, false, NT, false, ROWS>), grid, dim3(FD_THREADS), lds, s, fa, ea, fem_blocks);
   else if (fa.pw_kind && energy)
     hipLaunchKernelGGL((step_kernel<false, true, NT, true>), grid, dim3(FD_THREADS), lds, s, fa, ea, fem_blocks);
   else if (fa.pw_kind)
-    hipLaunchKernelGGL((step_kernel<false, false, NT, true>), grid, dim3(FD_THREADS), lds, s, fa, ea, fem_blocks);
+    hipLaunchKernelGGL((step_kernel<false, false, NT, true, ROWS>), grid, dim3(FD_THREADS), lds, s, fa, ea, fem_blocks);
   else if (energy)
     hipLaunchKernelGGL((step_kernel<false, true, NT>), grid, dim3(FD_THREADS), lds, s, fa, ea, fem_blocks);
   else
-    hipLaunchKernelGGL((step_kernel<false, false, NT>), grid, dim3(FD_THREADS), lds, s, fa, ea, fem_blocks);
+    hipLaunchKernelGGL((step_kernel<false, false, NT, false, ROWS>), grid, dim3(FD_THREADS), lds, s, fa, ea, fem_blocks);
 }
 
 template <bool NT>
@@ -1995,9 +2019,11 @@ void launch_step_pair(const FdArgs& fa, const FemArgs& ea, hipStream_t s, bool a
 void launch_step(const FdArgs& fa, const FemArgs& ea, hipStream_t s, bool adj, bool energy, bool nt,
                  const PgArgs* pg) {
   if (nt)
-    launch_step_t<true>(fa, ea, s, adj, energy, pg);
+    launch_step_t<true, true>(fa, ea, s, adj, energy, pg);
+  else if (fa.rows)
+    launch_step_t<false, true>(fa, ea, s, adj, energy, pg);
   else
-    launch_step_t<false>(fa, ea, s, adj, energy, pg);
+    launch_step_t<false, false>(fa, ea, s, adj, energy, pg);
 }
 
 template <bool NT, bool GEOM, bool GATHER>
