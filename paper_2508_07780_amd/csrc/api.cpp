@@ -18,6 +18,7 @@
 #include "paper_grad.hpp"
 #include "dd_common.hpp"
 #include "resident.hpp"
+#include "resident_order.hpp"
 
 using namespace dd;
 
@@ -666,62 +667,55 @@ constexpr int64_t kGraphAutoNodes = int64_t(1) << 19;
 
 // ---- resident solves ------------------------------------------------------------------------------
 
-// Resident launches in flight on one GPU together have at most a block per CU: with more, each would hold some of the
-// places the other waits for, and be called off.  (Another process's can still be in the way: then the
-// launch's own protocol decides.)  One entry per stream that queued some, the newest last, bounded.
-struct ResFlight {
-  hipStream_t stream;
-  hipEvent_t end;       // after the stream's newest resident launch
-  int blocks;           // of its largest
+// This thread may make calls that another thread's capture in global mode would forbid (queries, allocations):
+// nothing of what is done under the guard belongs to a capture.
+struct CaptureRelaxed {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  CaptureRelaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~CaptureRelaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
 };
+
+// The resident launches in flight per GPU (resident_order.hpp).  Another process's can still be in the way: then the
+// launch's own protocol decides.
 struct ResOrder {
   std::mutex lock;
-  std::vector<ResFlight> flights;
+  ResFlights<hipStream_t, hipEvent_t> flights;
 };
-constexpr size_t kResFlights = 32;
 ResOrder& res_order() {
   static ResOrder order[64];
   int dev = 0;
   (void)hipGetDevice(&dev);
   return order[dev & 63];
 }
-// Held while a call queues resident launches of `blocks` blocks on `st`: the stream first waits for the newest entries
-// that leave it no room and for all before them.
+// Held while a call queues resident launches of `blocks` blocks on `st`, which first waits for those that leave it no
+// room.
 struct ResQueue {
   ResOrder* o = nullptr;
   hipStream_t st;
-  ResFlight mine{};
+  hipEvent_t end = nullptr;
+  int counts = 0;
   ResQueue(int blocks, hipStream_t s) : st(s) {
     if (!blocks) return;
     o = &res_order();
     o->lock.lock();
-    std::vector<ResFlight>& f = o->flights;
-    mine = {st, nullptr, blocks};
-    int room = device_cus() - blocks;
-    size_t first = f.size();                      // entries from here on may run beside this call's
-    while (first > 0 && (f[first - 1].stream == st || room >= f[first - 1].blocks)) {
-      --first;
-      if (f[first].stream != st) room -= f[first].blocks;
-    }
-    for (size_t i = 0; i < f.size();) {
-      const bool own = f[i].stream == st;
-      if (i < first || own || f.size() >= kResFlights) {
-        (void)hipStreamWaitEvent(st, f[i].end, 0);
-        if (i < first) --first;
-        if (own && i >= first) mine.blocks = std::max(mine.blocks, f[i].blocks);   // may still be running
-        if (mine.end) (void)hipEventDestroy(f[i].end);
-        else mine.end = f[i].end;
-        f.erase(f.begin() + i);
-      } else {
-        ++i;
-      }
-    }
+    const CaptureRelaxed relaxed;
+    counts = o->flights.admit(
+        st, blocks, device_cus(),
+        [](hipEvent_t e) {
+          const hipError_t q = hipEventQuery(e);
+          if (q == hipErrorNotReady && hipPeekAtLastError() == hipErrorNotReady) (void)hipGetLastError();
+          return q == hipSuccess;
+        },
+        [&](hipEvent_t e) { (void)hipStreamWaitEvent(st, e, 0); },
+        [&](hipEvent_t e) {
+          if (end) (void)hipEventDestroy(e);
+          else end = e;
+        });
   }
   ~ResQueue() {
     if (!o) return;
-    if ((mine.end || hipEventCreateWithFlags(&mine.end, hipEventDisableTiming) == hipSuccess) &&
-        hipEventRecord(mine.end, st) == hipSuccess)
-      o->flights.push_back(mine);
+    if ((end || hipEventCreateWithFlags(&end, hipEventDisableTiming) == hipSuccess) && hipEventRecord(end, st) == hipSuccess)
+      o->flights.add(st, end, counts);
     o->lock.unlock();
   }
 };

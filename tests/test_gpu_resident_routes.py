@@ -2,6 +2,7 @@
 
 * every variant of the resident kernels takes its solves itself, and equals the launches;
 * a called-off launch's solves are taken by the fallback kernel;
+* launches of unequal sizes on several streams are not called off;
 * a solve whose launch is called off, with the streaming variant of the launches forced
   (DD_FD_NT=1): the kernel that takes it lays out its own blocks.
 """
@@ -75,3 +76,30 @@ def test_called_off_solves_are_taken(name, monkeypatch):
         s = p.resident_stats(which)
         assert s["solves"] == 0 and s["fallback"] == _solves(1)[which] and s["called_off"] >= s["fallback"], (which, s)
     p.close()
+
+
+def test_unequal_launches_on_three_streams(monkeypatch):
+    """One launch that fills the GPU for a while and two small ones that fit beside each other, not beside it."""
+    import copy
+    import torch
+    long = copy.deepcopy(problem("f4"))
+    long[0].n_steps = 60000
+    long[0].ckpt_every = 60000
+    forms = [long, _form("one_over"), _form("one_over")]
+    ps = [_problem(torch, monkeypatch, f, 1) for f in forms]
+    want = ps[1].forward(forms[1][3][:1], save=False).clone()
+    ps[2].forward(forms[2][3][:1], save=False)
+    out = [torch.empty((1, p.n_steps, p.n_det, 3), dtype=torch.float32, device="cuda") for p in ps]
+    streams = [torch.cuda.Stream() for _ in ps]
+    torch.cuda.synchronize()
+    for p, f, o, s in zip(ps, forms, out, streams):
+        with torch.cuda.stream(s):
+            p.forward(f[3][:1], save=False, out=o)
+    torch.cuda.synchronize()
+    stats = [p.resident_stats("forward") for p in ps]
+    print("[gpu]", stats, flush=True)
+    assert stats[0]["blocks"] > 256 - stats[1]["blocks"] and 2 * stats[1]["blocks"] <= 256
+    assert [s["called_off"] for s in stats] == [0, 0, 0]
+    assert torch.equal(out[1], want) and torch.equal(out[2], want)
+    for p in ps:
+        p.close()
