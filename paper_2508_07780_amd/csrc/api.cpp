@@ -798,7 +798,8 @@ ResArgs res_args(const dd_problem* p, const ResDevice& r) {
   ResArgs a = r.a;
   a.ctl = p->res_ctl;
   a.need = p->res_mode == 2 ? r.n_blocks + 1 : r.n_blocks;
-  a.wait_ticks = p->res_mode == 2 ? 1000 : 10000000;   // 0.1 s for the blocks to get their places
+  // for the blocks to get their places: about what the launches would take, 1 ms to 0.1 s
+  a.wait_ticks = p->res_mode == 2 ? 1000 : std::min(std::max(1000ll * p->d.n_steps, 100000ll), 10000000ll);
   a.run_ticks = 400000000 + 100000 * (long long)p->d.n_steps;   // 4 s and 1 ms per step without an end: given up
   a.nx = p->nx; a.ny = p->ny; a.nz = p->nz; a.nt = p->d.n_steps;
   a.N = p->N; a.n_l0 = p->n_l0; a.n_own = p->n_own; a.n_det = p->n_det;
@@ -884,9 +885,9 @@ int res_forward(dd_problem* p, const dd_source& src, int s, float* traces, bool 
       }
     }
   a.n_tab = (int)tab.size();
-  launch_resident_begin(a, tab.data(), a.n_tab, st);
+  launch_resident_begin(a, s == 0, tab.data(), a.n_tab, st);
   launch_resident(a, p->res_fwd.plan, st);
-  launch_resident_serial(a, fd_base(p), fem_base(p), false, st);
+  launch_resident_rest(a, fd_base(p), fem_base(p), false, st);
   return check_launch(p);
 }
 
@@ -906,9 +907,9 @@ int res_adjoint(dd_problem* p, int s, const float* cot, const float* obs, hipStr
   const FemArgs f = fem_base(p);
   a.inv_dt2 = f.inv_dt2;
   a.inv_2dt = f.inv_2dt;
-  launch_resident_begin(a, nullptr, 0, st);
+  launch_resident_begin(a, s == 0, nullptr, 0, st);
   launch_resident(a, p->res_adj.plan, st);
-  launch_resident_serial(a, fd_base(p), f, true, st);
+  launch_resident_rest(a, fd_base(p), f, true, st);
   return check_launch(p);
 }
 
@@ -1898,7 +1899,7 @@ int dd_resident_stats(dd_problem* p, int32_t which, dd_resident_info* out, void*
     return fail(p, DD_ERR_HIP, "readback failed");
   out->solves = c.solves[which];
   out->called_off = c.called_off[which];
-  out->fallback = c.serial[which];
+  out->fallback = c.fallback[which];
   return DD_OK;
 }
 

@@ -13,6 +13,9 @@
 //     lambda^{k-1} = lambda^k + Lambda^k.
 // Field state is FP32; the energy and gradient sums are FP64.
 #include "dd_common.hpp"
+
+#include <type_traits>
+
 #include "kuhn_star.hpp"
 #include "oblique.hpp"
 #include "pg_tile.hpp"
@@ -2118,106 +2121,169 @@ void launch_count_nonfinite(const float* x, int64_t n, int* err, hipStream_t s) 
 }
 
 // ---------------------------------------------------------------------------------------
-// A resident solve's last resort (resident.hpp): one block takes every step with the tiles and partitions of the
-// step kernels, one after another, unless the solve is done.  It waits for no other block.  A few
-// hundred times slower than the resident kernel; it only runs where that was called off twice.
+// A resident solve's last resort (resident.hpp), where its launch was called off: the steps by the tiles and partitions of
+// the step kernels, in one launch of any number of blocks, of which any number may be on the GPU.  Blocks take
+// tickets in the order of the work; a ticket's work waits until all work of the steps before is done.  That
+// was given out earlier, to blocks that are running and wait for yet earlier work only: every wait ends, with one block
+// as with all of them.  Work is handed from block to block through memory: one wave's fences of the GPU's scope around
+// each ticket's, which bound a step: one block per CU, and few, large tickets.  us per step, forward / adjoint, with a block
+// per CU: 25^3 11.5 / 12.2 (by launches 5.5 / 5.9), 37x35x41 with recompute 18.9 / 25.8 (5.1 / 8.3), 64^3 32.6 / 31.1 (6.6 /
+// 6.6), 96^3 with recompute 53.7 / 74.6 (10.6 / 13.2); with two blocks per CU and twice the tickets 15.7 / 16.0, 35.9 / 42.9, 58.6 /
+// 54.7, 85.7 / 116.8; fences by all waves 90 / 96 at 64^3; one block for everything 157 / 180, 272 / 319, 1620 / 1799, 3746 / 5049.
 // ---------------------------------------------------------------------------------------
+constexpr int REST_TICKETS = 128;   // of a step: for its partitions, and for its row blocks, at most
+constexpr int REST_CHUNKS = 64;     // tickets of a fill or copy
+struct RestWork {
+  enum { FILL, STEP, COPY, RECOMPUTE, END };
+  int kind;
+  int64_t seg, k;          // adjoint: segment; level of the step
+  int64_t base, size;      // tickets [base, base + size)
+};
 template <bool ADJ>
-__global__ __launch_bounds__(FD_THREADS) void resident_serial_kernel(ResArgs a, FdArgs fa, FemArgs ea) {
+__device__ __forceinline__ void rest_next(const ResArgs& a, int step, int parts, RestWork& w) {
+  w.base += w.size;
+  const int64_t k0 = w.seg * a.K;
+  if (!ADJ) {
+    if (w.kind == RestWork::STEP) ++w.k;
+    w.kind = w.k < a.nt ? RestWork::STEP : RestWork::END;
+  } else if (w.kind == RestWork::FILL) {
+    w.kind = RestWork::STEP;                          // the last segment's levels are saved
+    w.seg = a.nseg - 1;
+    w.k = a.nt;
+  } else if (w.kind == RestWork::COPY) {
+    w.kind = RestWork::RECOMPUTE;
+    w.k = k0;
+  } else if (w.kind == RestWork::RECOMPUTE) {
+    if (++w.k == k0 + a.K) w.kind = RestWork::STEP;   // down from level k0 + K
+  } else if (--w.k == k0) {
+    w.kind = --w.seg >= 0 ? RestWork::COPY : RestWork::END;
+  }
+  w.size = w.kind == RestWork::STEP ? step : w.kind == RestWork::RECOMPUTE ? parts : REST_CHUNKS;
+}
+
+template <bool ADJ>
+__global__ __launch_bounds__(FD_THREADS) void resident_rest_kernel(ResArgs a, FdArgs fa, FemArgs ea) {
 #pragma clang fp contract(off)
-  const int tid = threadIdx.x, state = a.ctl->state;
-  if (tid == 0) {
-    if (state == RES_DONE) ++a.ctl->solves[ADJ];
-    else ++a.ctl->called_off[ADJ], ++a.ctl->serial[ADJ];
+  __shared__ unsigned long long mine;
+  const int tid = threadIdx.x;
+  if (a.ctl->state == RES_DONE) {
+    if (blockIdx.x == 0 && tid == 0) ++a.ctl->solves[ADJ];
+    return;
   }
-  if (state == RES_DONE) return;
   const int64_t n_own = a.n_own, n_l0 = a.n_l0;
-  auto zero = [&](float* p, int64_t n) {
-    for (int64_t i = tid; i < n; i += FD_THREADS) p[i] = 0.f;
-  };
-  for (int b = 0; b < 2; ++b) {
-    zero(a.Efd[b], 3 * a.N);
-    zero(a.Efem[b], 3 * n_own);
-  }
-  zero(a.Vfem, 3 * n_own);
-  zero(a.iring, 6 * n_l0);
-  if (!ADJ && a.ihist) {
-    zero(a.ihist, 3 * n_l0);
-    zero(a.ckpt, 6 * n_own);
-    if (a.k_tail == 0) zero(a.tail, 6 * n_own);
-  }
-  auto fem = [&](const FemArgs& e, bool adj) {
-    for (int p = 0; p < e.n_part; ++p) {
-      __syncthreads();
-      if (adj) fem_stencil_part<true, false>(e, p);
-      else fem_stencil_part<false, false>(e, p);
-    }
-    __syncthreads();
-  };
-  auto tiles = [&]() {
-    for (int b = 0; b < fa.row_per_xcd * N_XCD; ++b) fd_rows<ADJ, false, !ADJ>(fa, b);
-    __syncthreads();
-  };
+  // partitions and row blocks of a step, per ticket, and tickets of the partitions and of the whole step
+  const int rows = fa.row_per_xcd * N_XCD, row_n = (rows + REST_TICKETS - 1) / REST_TICKETS;
+  const int part_n = (ea.n_part + REST_TICKETS - 1) / REST_TICKETS, parts = (ea.n_part + part_n - 1) / part_n;
+  const int step = parts + (rows + row_n - 1) / row_n;
   fa.epart = ea.epart = nullptr;
   fa.X_prev = nullptr;
+  fa.rev = ea.rev = 0;
   ea.I_in = ea.I_out = a.Vfem;
   ea.ck_X = ea.ck_I = nullptr;
-  __syncthreads();
-  if (!ADJ) {
-    for (int n = 0; n < a.nt; ++n) {
-      const int cur = n & 1, nxt = cur ^ 1;
-      const double t = (double)n * a.dt;
-      fa.X_in = a.Efd[cur]; fa.X_out = a.Efd[nxt];
-      fa.rev = ea.rev = 0;
-      fa.top_a = fa.top_b = (a.abs_mask & DD_FACE_TOP) && t > a.t_switch;
-      const double pulse = n < a.n_tab ? a.tab[n] : 0.0;
-      const bool on = a.plane && t <= a.t_switch;
-      for (int c = 0; c < 3; ++c) {
-        fa.pw[c] = on && !a.oblique ? (float)(a.pw_scale * pulse * a.pol[c]) : 0.f;
-        fa.dip[c] = (float)(pulse * a.pol[c] * a.dip_scale);
-        fa.pw_amp[c] = a.pw_amp[c];
+  RestWork w{RestWork::FILL, 0, 0, 0, REST_CHUNKS};
+  for (;;) {
+    if (tid == 0) mine = __hip_atomic_fetch_add(&a.ctl->tickets, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int64_t t = (int64_t)mine;
+    while (w.kind != RestWork::END && t >= w.base + w.size) rest_next<ADJ>(a, step, parts, w);
+    if (w.kind == RestWork::END) break;
+    if (tid == 0) {
+      if (t == 0) {
+        ResCtl& c = *a.ctl;
+        ++c.fallback[ADJ];
+        if (!c.skip) ++c.called_off[ADJ];
+        c.skip = 1;
       }
-      fa.dip_idx = a.dip_idx;
-      fa.pw_kind = on && a.oblique ? a.kind : 0;
-      fa.pw_kx = a.pw_kx; fa.pw_ky = a.pw_ky; fa.pw_x0 = a.pw_x0; fa.pw_y0 = a.pw_y0;
-      fa.pw_omega = a.pw_omega; fa.pw_iw = a.pw_iw; fa.pw_sup = a.pw_sup;
-      fa.pw_t = a.kind == DD_SRC_GAUSS_SINE ? (float)(t - a.pw_t0) : (float)t;
-      fa.tr_out = a.traces + (int64_t)n * a.n_det * 3;
-      fa.cot_in = fa.obs_in = nullptr;
-      fa.iface_out = a.ihist ? a.ihist + (int64_t)(n + 1) * 3 * n_l0 : a.iring + nxt * 3 * n_l0;
-      ea.X_in = a.Efem[cur]; ea.X_out = a.Efem[nxt];
-      ea.iface_in = a.ihist ? a.ihist + (int64_t)n * 3 * n_l0 : a.iring + cur * 3 * n_l0;
-      ea.fd_out = a.Efd[nxt];
-      ea.ck_X = nullptr;
-      if (a.ckpt && n + 1 >= a.k_tail) ea.ck_X = a.tail + (n + 1 - a.k_tail) * 6 * n_own;
-      else if (a.ckpt && (n + 1) % a.K == 0 && (n + 1) / a.K < a.n_ck) ea.ck_X = a.ckpt + ((n + 1) / a.K) * 6 * n_own;
-      ea.ck_I = ea.ck_X ? ea.ck_X + 3 * n_own : nullptr;
-      fem(ea, false);
-      tiles();
+      while ((int64_t)__hip_atomic_load(&a.ctl->finished, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < w.base)
+        __builtin_amdgcn_s_sleep(1);
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
-  } else {
-    for (int64_t seg = a.nseg - 1; seg >= 0; --seg) {
-      const int64_t k0 = seg * a.K, k1 = min(k0 + a.K, (int64_t)a.nt);
-      float* win = seg == a.nseg - 1 ? a.tail : (seg & 1) ? a.win_b : a.win;
-      if (seg != a.nseg - 1) {
-        const float* ck = a.ckpt + seg * 6 * n_own;
-        for (int64_t i = tid; i < 6 * n_own; i += FD_THREADS) win[i] = ck[i];
-        FemArgs fw = ea;
-        fw.fd_out = nullptr;
-        fw.ck_X = fw.ck_I = nullptr;
-        for (int64_t k = k0; k < k1; ++k) {
-          fw.X_in = win + (k - k0) * 6 * n_own;
-          fw.X_out = win + (k - k0 + 1) * 6 * n_own;
-          fw.I_in = fw.X_in + 3 * n_own;
-          fw.I_out = fw.X_out + 3 * n_own;
-          fw.iface_in = a.ihist + k * 3 * n_l0;
-          fem(fw, false);
-        }
+    __syncthreads();
+    const int q = (int)(t - w.base);     // this ticket's share of the work
+    const int64_t first = (int64_t)q * FD_THREADS + tid, stride = (int64_t)REST_CHUNKS * FD_THREADS;
+    const auto zero = [&](float* p, int64_t n) {
+      for (int64_t i = first; i < n; i += stride) p[i] = 0.f;
+    };
+    const auto part_share = [&](const FemArgs& e, auto adj) {
+      for (int p = q * part_n; p < min((q + 1) * part_n, e.n_part); ++p) {
+        __syncthreads();
+        fem_stencil_part<decltype(adj)::value, false>(e, p);
       }
-      for (int64_t k = k1; k > k0; --k) {
-        const int cur = (int)(k & 1), prv = cur ^ 1;
+    };
+    float* win = w.seg == a.nseg - 1 ? a.tail : (w.seg & 1) ? a.win_b : a.win;
+    const int64_t k0 = w.seg * a.K;
+    if (w.kind == RestWork::FILL) {
+      for (int b = 0; b < 2; ++b) {
+        zero(a.Efd[b], 3 * a.N);
+        zero(a.Efem[b], 3 * n_own);
+      }
+      zero(a.Vfem, 3 * n_own);
+      zero(a.iring, 6 * n_l0);
+      if (!ADJ && a.ihist) {
+        zero(a.ihist, 3 * n_l0);
+        zero(a.ckpt, 6 * n_own);
+        if (a.k_tail == 0) zero(a.tail, 6 * n_own);
+      }
+    } else if (w.kind == RestWork::COPY) {
+      const float* ck = a.ckpt + w.seg * 6 * n_own;
+      for (int64_t i = first; i < 6 * n_own; i += stride) win[i] = ck[i];
+    } else if (w.kind == RestWork::RECOMPUTE) {
+      FemArgs fw = ea;
+      fw.fd_out = nullptr;
+      fw.X_in = win + (w.k - k0) * 6 * n_own;
+      fw.X_out = win + (w.k - k0 + 1) * 6 * n_own;
+      fw.I_in = fw.X_in + 3 * n_own;
+      fw.I_out = fw.X_out + 3 * n_own;
+      fw.iface_in = a.ihist + w.k * 3 * n_l0;
+      part_share(fw, std::false_type());
+    } else if (!ADJ) {
+      const int64_t n = w.k;
+      const int cur = (int)(n & 1), nxt = cur ^ 1;
+      const double time = (double)n * a.dt;
+      if (q < parts) {
+        ea.X_in = a.Efem[cur]; ea.X_out = a.Efem[nxt];
+        ea.iface_in = a.ihist ? a.ihist + n * 3 * n_l0 : a.iring + cur * 3 * n_l0;
+        ea.fd_out = a.Efd[nxt];
+        ea.ck_X = nullptr;
+        if (a.ckpt && n + 1 >= a.k_tail) ea.ck_X = a.tail + (n + 1 - a.k_tail) * 6 * n_own;
+        else if (a.ckpt && (n + 1) % a.K == 0 && (n + 1) / a.K < a.n_ck) ea.ck_X = a.ckpt + ((n + 1) / a.K) * 6 * n_own;
+        ea.ck_I = ea.ck_X ? ea.ck_X + 3 * n_own : nullptr;
+        part_share(ea, std::false_type());
+      } else {
+        fa.X_in = a.Efd[cur]; fa.X_out = a.Efd[nxt];
+        fa.top_a = fa.top_b = (a.abs_mask & DD_FACE_TOP) && time > a.t_switch;
+        const double pulse = n < a.n_tab ? a.tab[n] : 0.0;
+        const bool on = a.plane && time <= a.t_switch;
+        for (int c = 0; c < 3; ++c) {
+          fa.pw[c] = on && !a.oblique ? (float)(a.pw_scale * pulse * a.pol[c]) : 0.f;
+          fa.dip[c] = (float)(pulse * a.pol[c] * a.dip_scale);
+          fa.pw_amp[c] = a.pw_amp[c];
+        }
+        fa.dip_idx = a.dip_idx;
+        fa.pw_kind = on && a.oblique ? a.kind : 0;
+        fa.pw_kx = a.pw_kx; fa.pw_ky = a.pw_ky; fa.pw_x0 = a.pw_x0; fa.pw_y0 = a.pw_y0;
+        fa.pw_omega = a.pw_omega; fa.pw_iw = a.pw_iw; fa.pw_sup = a.pw_sup;
+        fa.pw_t = a.kind == DD_SRC_GAUSS_SINE ? (float)(time - a.pw_t0) : (float)time;
+        fa.tr_out = a.traces + n * a.n_det * 3;
+        fa.cot_in = fa.obs_in = nullptr;
+        fa.iface_out = a.ihist ? a.ihist + (n + 1) * 3 * n_l0 : a.iring + nxt * 3 * n_l0;
+        for (int b = (q - parts) * row_n; b < min((q - parts + 1) * row_n, rows); ++b) fd_rows<false, false, true>(fa, b);
+      }
+    } else {
+      const int64_t k = w.k;
+      const int cur = (int)(k & 1), prv = cur ^ 1;
+      if (q < parts) {
+        ea.X_in = a.Efem[cur]; ea.X_out = a.Efem[prv];
+        ea.iface_in = a.iring + cur * 3 * n_l0;
+        ea.fd_out = a.Efd[prv];
+        ea.wE = win + (k - k0) * 6 * n_own;
+        ea.wV = ea.wE + 3 * n_own;
+        ea.wVm = win + (k - 1 - k0) * 6 * n_own + 3 * n_own;
+        ea.g_eps = a.g_eps;
+        ea.g_sig = a.g_sig;
+        part_share(ea, std::true_type());
+      } else {
         fa.X_in = a.Efd[cur]; fa.X_out = a.Efd[prv];
-        fa.rev = ea.rev = 0;
         fa.top_a = (a.abs_mask & DD_FACE_TOP) && (double)(k - 1) * a.dt > a.t_switch;
         fa.top_b = (a.abs_mask & DD_FACE_TOP) && (double)(k + 1) * a.dt > a.t_switch;
         for (int c = 0; c < 3; ++c) fa.pw[c] = fa.dip[c] = 0.f;
@@ -2227,28 +2293,25 @@ __global__ __launch_bounds__(FD_THREADS) void resident_serial_kernel(ResArgs a, 
         fa.cot_in = a.cot + (k - 1) * a.n_det * 3;
         fa.obs_in = a.obs ? a.obs + (k - 1) * a.n_det * 3 : nullptr;
         fa.iface_out = a.iring + prv * 3 * n_l0;
-        ea.X_in = a.Efem[cur]; ea.X_out = a.Efem[prv];
-        ea.iface_in = a.iring + cur * 3 * n_l0;
-        ea.fd_out = a.Efd[prv];
-        ea.wE = win + (k - k0) * 6 * n_own;
-        ea.wV = ea.wE + 3 * n_own;
-        ea.wVm = win + (k - 1 - k0) * 6 * n_own + 3 * n_own;
-        ea.g_eps = a.g_eps;
-        ea.g_sig = a.g_sig;
-        fem(ea, true);
-        tiles();
+        for (int b = (q - parts) * row_n; b < min((q - parts + 1) * row_n, rows); ++b) fd_rows<true, false>(fa, b);
       }
+    }
+    __syncthreads();
+    if (tid == 0) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      __hip_atomic_fetch_add(&a.ctl->finished, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 }
 
-void launch_resident_serial(const ResArgs& a, const FdArgs& fa, const FemArgs& ea, bool adj, hipStream_t s) {
+void launch_resident_rest(const ResArgs& a, const FdArgs& fa, const FemArgs& ea, bool adj, hipStream_t s) {
   FdArgs f = fa;
   fd_row_grid(f, false);      // the kernel's z-chunk, whichever one the problem's launches take
+  const dim3 grid(device_cus());
   if (adj)
-    hipLaunchKernelGGL((resident_serial_kernel<true>), dim3(1), dim3(FD_THREADS), stencil_lds(ea), s, a, f, ea);
+    hipLaunchKernelGGL((resident_rest_kernel<true>), grid, dim3(FD_THREADS), stencil_lds(ea), s, a, f, ea);
   else
-    hipLaunchKernelGGL((resident_serial_kernel<false>), dim3(1), dim3(FD_THREADS), stencil_lds(ea), s, a, f, ea);
+    hipLaunchKernelGGL((resident_rest_kernel<false>), grid, dim3(FD_THREADS), stencil_lds(ea), s, a, f, ea);
 }
 
 }  // namespace dd

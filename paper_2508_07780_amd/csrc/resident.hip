@@ -924,9 +924,6 @@ __device__ __forceinline__ void fem_brick(const ResArgs& a, const ResBlock& b, f
 template <int RUN, bool ADJ, bool REC>
 __global__ __launch_bounds__(RES_THREADS) void resident_kernel(ResArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
-  // done, or called off after this attempt was queued: nothing to do
-  const int s = load_state(a.ctl);
-  if (s == RES_DONE || s == RES_FAILED) return;
   if (!assemble(a)) return;
   const long long limit = wall_clock64() + a.run_ticks;
   const ResBlock b = a.blocks[blockIdx.x];
@@ -936,39 +933,31 @@ __global__ __launch_bounds__(RES_THREADS) void resident_kernel(ResArgs a) {
 }
 
 struct TabChunk { double v[RES_TAB]; };
-__global__ void resident_begin_kernel(ResCtl* c, int tags, double* tab, int off, int n, TabChunk v) {
+__global__ void resident_begin_kernel(ResCtl* c, int tags, bool first, double* tab, int off, int n, TabChunk v) {
   if (off == 0 && threadIdx.x == 0) {
     c->epoch += tags;
-    c->arrive = c->state = c->end = 0;
+    c->arrive = c->end = 0;
+    c->tickets = c->finished = 0;
+    if (first) c->skip = 0;
+    c->state = c->skip ? RES_OFF : RES_WAIT;
   }
   for (int i = threadIdx.x; i < n; i += blockDim.x) tab[off + i] = v.v[i];
 }
-// between two attempts: forget one that was called off
-__global__ void resident_retry_kernel(ResCtl* c, int adj) {
-  if (c->state == RES_OFF) {
-    c->arrive = c->state = c->end = 0;
-    ++c->called_off[adj];
-  }
-}
-
 template <int RUN, bool ADJ, bool REC>
 void launch_t(const ResArgs& a, size_t lds, hipStream_t s) {
   (void)hipFuncSetAttribute((const void*)resident_kernel<RUN, ADJ, REC>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  for (int i = 0; i < 2; ++i) {
-    if (i) hipLaunchKernelGGL(resident_retry_kernel, dim3(1), dim3(1), 0, s, a.ctl, ADJ ? 1 : 0);
-    hipLaunchKernelGGL((resident_kernel<RUN, ADJ, REC>), dim3(a.n_blocks), dim3(RES_THREADS), lds, s, a);
-  }
+  hipLaunchKernelGGL((resident_kernel<RUN, ADJ, REC>), dim3(a.n_blocks), dim3(RES_THREADS), lds, s, a);
 }
 
 }  // namespace
 
-void launch_resident_begin(const ResArgs& a, const double* tab, int n, hipStream_t s) {
+void launch_resident_begin(const ResArgs& a, bool first, const double* tab, int n, hipStream_t s) {
   int off = 0;
   do {
     TabChunk v;
     const int m = std::min(n - off, RES_TAB);
     for (int i = 0; i < m; ++i) v.v[i] = tab[off + i];
-    hipLaunchKernelGGL(resident_begin_kernel, dim3(1), dim3(512), 0, s, a.ctl, 2 * a.nt + 64, const_cast<double*>(a.tab), off,
+    hipLaunchKernelGGL(resident_begin_kernel, dim3(1), dim3(512), 0, s, a.ctl, 2 * a.nt + 64, first, const_cast<double*>(a.tab), off,
                        m, v);
     off += m;
   } while (off < n);

@@ -17,9 +17,9 @@
 // Blocks wait for each other, so all of them must be on the GPU at once.  Each announces
 // itself first, and the last one to arrive starts the solve for all; if some do not get a place
 // in time (the GPU is shared with other work), the launch is called off before anything is
-// written, a second attempt follows, and after that a kernel of one block, which waits for
-// nobody, takes all steps.  The state of the attempt is decided by compare-and-swap, so every block
-// sees the same outcome; waits during the solve are bounded the same way.
+// written, and a kernel that needs no number of blocks at once takes all steps, at about the launches' rate.  The
+// state is decided by compare-and-swap, so every block sees the same outcome; waits during the solve are bounded the
+// same way.
 #pragma once
 
 #include "dd_common.hpp"
@@ -79,9 +79,11 @@ __host__ __device__ inline ResRows res_rows(const int* dim, int run, int t) {
 struct ResCtl {
   unsigned epoch;              // tag of level 0 of the current solve
   int arrive, state, end;      // RES_WAIT .. RES_DONE
+  unsigned long long tickets, finished;   // of the last resort
+  int skip;                    // a launch of this call has been called off: its other solves go to the last resort
   // per direction (forward, adjoint): solves taken by the resident kernel, launches called off, solves taken by the
-  // one-block kernel
-  int solves[2], called_off[2], serial[2];
+  // last resort
+  int solves[2], called_off[2], fallback[2];
 };
 enum { RES_WAIT = 0, RES_GO = 1, RES_OFF = 2, RES_FAILED = 3, RES_DONE = 4 };
 
@@ -170,10 +172,11 @@ bool resident_fits(const dd_problem_desc& d, int cus);
 // Bytes of such a plan's device arrays and exchange words, at most.
 size_t resident_bytes_bound(const dd_problem_desc& d, int cus, bool adj, bool rec);
 
-void launch_resident_begin(const ResArgs& a, const double* tab, int n, hipStream_t s);
+// first: the call's first solve.
+void launch_resident_begin(const ResArgs& a, bool first, const double* tab, int n, hipStream_t s);
 void launch_resident(const ResArgs& a, const ResPlan& plan, hipStream_t s);
-// The one-block kernel: takes all steps unless the solve is done (kernels.hip).
-void launch_resident_serial(const ResArgs& a, const FdArgs& fa, const FemArgs& ea, bool adj, hipStream_t s);
+// The last resort: takes all steps unless the solve is done (kernels.hip).
+void launch_resident_rest(const ResArgs& a, const FdArgs& fa, const FemArgs& ea, bool adj, hipStream_t s);
 int device_cus();
 
 }  // namespace dd

@@ -1,11 +1,13 @@
 """Which kernel takes a resident solve, and that each of them equals the launches bit for bit.
 
 * every variant of the resident kernels takes its solves itself, and equals the launches;
-* a called-off launch's solves are taken by the fallback kernel;
+* a called-off launch's solves are taken by the fallback kernel, at a rate near the launches';
 * launches of unequal sizes on several streams are not called off;
 * a solve whose launch is called off, with the streaming variant of the launches forced
   (DD_FD_NT=1): the kernel that takes it lays out its own blocks.
 """
+
+import math
 
 import pytest
 
@@ -103,3 +105,29 @@ def test_unequal_launches_on_three_streams(monkeypatch):
     assert torch.equal(out[1], want) and torch.equal(out[2], want)
     for p in ps:
         p.close()
+
+
+def test_called_off_solves_keep_their_rate(monkeypatch):
+    """A solve whose launch was called off takes a few times as long as by launches (5 measured), not hundreds."""
+    import time
+    import torch
+    form = problem("cube64")
+    form[0].n_steps = form[0].ckpt_every = 200
+    took = []
+    for mode in (0, 2):
+        p = _problem(torch, monkeypatch, form, mode)
+        tr = p.forward(form[3][1:], save=True).clone()
+        best = math.inf
+        for _ in range(3):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            p.forward(form[3][1:], save=True, out=tr)
+            p.adjoint(tr)
+            torch.cuda.synchronize()
+            best = min(best, time.perf_counter() - t0)
+        if mode:
+            assert p.resident_stats("forward")["fallback"] == p.resident_stats("adjoint")["fallback"] + 1 == 4
+        took.append(best)
+        p.close()
+    print(f"[gpu] {took[0] * 1e3:.2f} ms by launches, {took[1] * 1e3:.2f} ms called off", flush=True)
+    assert took[1] <= 30 * took[0]
