@@ -213,7 +213,8 @@ int dd_meshref_result(const dd_refinement* r, uint8_t* marks, double* extra_xyz,
 int dd_meshref_interpolate(const dd_refinement* r, const float* in, float* out);
 int dd_meshref_destroy(dd_refinement* r);
 /* Releases the problem.  With hipMalloc memory the device is synchronised first; with a
- * caller allocator only the library's own second stream is, and each buffer goes back
+ * caller allocator only the library's own second stream and the problem's last graph replays
+ * and resident solve (dd_set_graph, dd_resident_stats) are waited for, and each buffer goes back
  * through free_fn while the caller's stream may still hold queued work that reads it: the
  * allocator must order reuse after that work (a stream-ordered caching allocator on the
  * stream of the calls does). */
@@ -365,7 +366,7 @@ int dd_misfit_noalloc(dd_problem* p, const float* traces_dev, const float* obs_d
  * launch by launch.  DD_GRAPH_OFF: launch by launch.  Results are bitwise those of the
  * launch-by-launch calls.  Not while kernel timing (dd_profile_enable) is on, nor with the
  * two-stream step order.  A re-capture waits for the previous replay of that graph to
- * finish, and dd_destroy for the last replays of the problem's graphs.  The environment variable DD_GRAPH (0, 1, 2) sets the mode of problems created
+ * finish, and dd_destroy for the last replays of the problem's graphs and its last resident solve.  The environment variable DD_GRAPH (0, 1, 2) sets the mode of problems created
  * after it. */
 enum { DD_GRAPH_OFF = 0, DD_GRAPH_ON = 1, DD_GRAPH_AUTO = 2 };
 int dd_set_graph(dd_problem* p, int32_t mode);
@@ -376,7 +377,8 @@ int dd_graph_stats(const dd_problem* p, int32_t which, int64_t* captures, int64_
 /* Resident solves (all time steps of a source in one launch, on grids that fit on chip), for which =
  * DD_GRAPH_FORWARD or DD_GRAPH_ADJOINT: solves taken so far, launches called off because their blocks did not all
  * get a place on the GPU, and solves that another kernel took after that; and the plan in use (all 0: none): blocks,
- * planes per thread, nodes of the largest finite-element block.  Waits for `stream`. */
+ * planes per thread, nodes of the largest finite-element block.  After a launch was called off, the problem's next 16
+ * solves (32, 64, .. 1024 after further ones) run by launches.  Waits for `stream`. */
 typedef struct dd_resident_info {
   int64_t solves, called_off, fallback;
   int32_t blocks, run, fem_nodes;

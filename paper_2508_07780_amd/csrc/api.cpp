@@ -135,11 +135,17 @@ struct dd_problem {
   ResCtl* res_ctl = nullptr;
   double* res_tab = nullptr;
   bool res_ready = false;       // the control block has been cleared
+  // launches called off, written by the GPU (host memory); how many the host knows of; solves still to run by launches
+  // for it, and how many it will be next time; an event after the last resident solve
+  int* res_off = nullptr;
+  int res_off_seen = 0;
+  int64_t res_pause = 0, res_pause_next = 16;
+  hipEvent_t res_end = nullptr;
   std::vector<int> res_own_api; // what the plans are built from; empty: not eligible
   bool kuhn = false;            // the assembled stencil is the Kuhn star, of these values
   StarValues star{};
   int res_mode = -1;            // DD_RESIDENT: 0 off, 1 from the first call on, 2 as 1 but every launch is called off
-                                // (a test of the last resort); else once the plan pays
+                                // (a test of the last resort), 3 as 2 but the pauses are kept; else once the plan pays
   std::string err;
   std::vector<void*> allocs;
   // kernel timing: event pairs around each step launch, per launch kind
@@ -762,6 +768,15 @@ int res_create(dd_problem* p, bool adj, ResDevice& r, hipStream_t st) {
   if (int rc = dalloc(p, &r.a.xbuf, (size_t)RES_RING * 3 * q.n_pub)) return rc;
   if (rec)
     if (int rc = dalloc(p, &r.a.xbuf_rec, (size_t)RES_RING * 3 * q.n_pub)) return rc;
+  if (!p->res_end && hipEventCreateWithFlags(&p->res_end, hipEventDisableTiming) != hipSuccess)
+    return fail(p, DD_ERR_HIP, "event creation failed");
+  if (!p->res_off) {
+    if (hipHostMalloc((void**)&p->res_off, sizeof(int), hipHostMallocDefault) != hipSuccess) {
+      p->res_off = nullptr;
+      return fail(p, DD_ERR_OOM, "host allocation failed");
+    }
+    *p->res_off = 0;
+  }
   if (!p->res_ctl)
     if (int rc = dalloc(p, &p->res_ctl, 1)) return rc;
   if (!p->res_tab)
@@ -797,9 +812,10 @@ void res_prepare(dd_problem* p, ResDevice& r, hipStream_t st) {
 ResArgs res_args(const dd_problem* p, const ResDevice& r) {
   ResArgs a = r.a;
   a.ctl = p->res_ctl;
-  a.need = p->res_mode == 2 ? r.n_blocks + 1 : r.n_blocks;
+  a.off_host = p->res_off;
+  a.need = p->res_mode >= 2 ? r.n_blocks + 1 : r.n_blocks;
   // for the blocks to get their places: about what the launches would take, 1 ms to 0.1 s
-  a.wait_ticks = p->res_mode == 2 ? 1000 : std::min(std::max(1000ll * p->d.n_steps, 100000ll), 10000000ll);
+  a.wait_ticks = p->res_mode >= 2 ? 1000 : std::min(std::max(1000ll * p->d.n_steps, 100000ll), 10000000ll);
   a.run_ticks = 400000000 + 100000 * (long long)p->d.n_steps;   // 4 s and 1 ms per step without an end: given up
   a.nx = p->nx; a.ny = p->ny; a.nz = p->nz; a.nt = p->d.n_steps;
   a.N = p->N; a.n_l0 = p->n_l0; a.n_own = p->n_own; a.n_det = p->n_det;
@@ -845,7 +861,23 @@ bool res_wanted(dd_problem* p, bool adj, int n_src, bool again, hipStream_t st) 
       p->err = err;
     }
   }
-  return r.n_blocks > 0;
+  if (!r.n_blocks) return false;
+  // The GPU is shared with work that leaves the blocks no place: launches for a while, longer each time (a call that finds no
+  // place costs about the launches' time for the wait and two to five times it for its solves).
+  const int off = __atomic_load_n(p->res_off, __ATOMIC_RELAXED);
+  if (off != p->res_off_seen) {
+    p->res_off_seen = off;
+    p->res_pause = p->res_pause_next;
+    p->res_pause_next = std::min<int64_t>(2 * p->res_pause_next, 1024);
+  }
+  if (p->res_pause <= 0 || p->res_mode == 2) return true;
+  p->res_pause -= n_src;
+  return false;
+}
+
+// After the resident solves of a call: dd_destroy waits for them (they write to the problem's host word).
+int res_mark(dd_problem* p, hipStream_t st) {
+  return hipEventRecord(p->res_end, st) == hipSuccess ? DD_OK : fail(p, DD_ERR_HIP, "event record failed");
 }
 
 int res_forward(dd_problem* p, const dd_source& src, int s, float* traces, bool save, hipStream_t st) {
@@ -1579,6 +1611,11 @@ int dd_destroy(dd_problem* p) {
   if (p->aux) (void)hipStreamDestroy(p->aux);
   graph_free(p->gfwd);
   graph_free(p->gadj);
+  if (p->res_end) {
+    (void)hipEventSynchronize(p->res_end);
+    (void)hipEventDestroy(p->res_end);
+  }
+  if (p->res_off) (void)hipHostFree(p->res_off);
   if (p->cap) (void)hipStreamDestroy(p->cap);
   for (void* q : p->allocs) raw_free(p->free_fn, p->actx, q);
   delete p;
@@ -1678,6 +1715,8 @@ int dd_forward(dd_problem* p, const dd_source* src, int32_t n_src, float* traces
       if (rc) return rc;
     }
   }
+  if (res)
+    if (int rc = res_mark(p, st)) return rc;
   if (save) {
     p->saved = true;
     p->saved_n_src = n_src;
@@ -1727,6 +1766,8 @@ int adjoint_all(dd_problem* p, const float* cot, const float* obs, hipStream_t s
     int rc = adjoint_launches(p, cot, obs, res, st);
     if (rc) return rc;
   }
+  if (res)
+    if (int rc = res_mark(p, st)) return rc;
   p->have_grad = true;
   p->have_pg = p->pg_on || p->r2;
   return DD_OK;

@@ -2193,6 +2193,7 @@ __global__ __launch_bounds__(FD_THREADS) void resident_rest_kernel(ResArgs a, Fd
         ++c.fallback[ADJ];
         if (!c.skip) ++c.called_off[ADJ];
         c.skip = 1;
+        __hip_atomic_store(a.off_host, c.called_off[0] + c.called_off[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       }
       while ((int64_t)__hip_atomic_load(&a.ctl->finished, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < w.base)
         __builtin_amdgcn_s_sleep(1);

@@ -116,6 +116,7 @@ struct ResArgs {
   const uint32_t* out_cell; const int* out_idx; const int2* fem_node;
   unsigned long long *xbuf, *xbuf_rec;   // [RES_RING][3][n_pub]; the recompute's words
   ResCtl* ctl;
+  int* off_host;                         // host word: launches called off so far
   int n_pub, n_blocks, need;
   long long wait_ticks, run_ticks;       // bounds of the waits (100 MHz clock)
   int nx, ny, nz, nt;

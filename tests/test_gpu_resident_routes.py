@@ -131,3 +131,25 @@ def test_called_off_solves_keep_their_rate(monkeypatch):
         p.close()
     print(f"[gpu] {took[0] * 1e3:.2f} ms by launches, {took[1] * 1e3:.2f} ms called off", flush=True)
     assert took[1] <= 30 * took[0]
+
+
+def test_launches_for_a_while_after_a_call_off(monkeypatch):
+    """A problem whose launch was called off runs its next 16 solves by launches, then tries again, and pauses for 32."""
+    import torch
+    form = _form("minimal")
+    ref = _problem(torch, monkeypatch, form, 0)
+    want = ref.forward(form[3], save=True).clone()
+    p = _problem(torch, monkeypatch, form, 3)
+    tries = []
+    for _ in range(30):                              # two solves each
+        before = p.resident_stats("forward")
+        out = p.forward(form[3], save=True)
+        torch.cuda.synchronize()
+        after = p.resident_stats("forward")
+        assert torch.equal(out, want)
+        tries.append((after["called_off"] - before["called_off"], after["fallback"] - before["fallback"]))
+    # the second solve of a call that was called off does not wait again
+    assert tries[0] == tries[9] == tries[26] == (1, 2)
+    assert sum(t != (0, 0) for t in tries) == 3
+    p.close()
+    ref.close()
