@@ -232,8 +232,11 @@ int dd_detector_nodes(const dd_problem_desc* desc, int64_t* out, int64_t capacit
  * optional buffer (initial data, the div-div form R2 / paper-formula gradient, the misfit's
  * weights and partials, a dd_cga run, the plans of solves that run resident: up to about three million
  * grid nodes, built by the forward or adjoint call by which they pay), for admission control.  0 for
- * an invalid descriptor. */
+ * an invalid descriptor.  Up to 0.1 ms of host time where a plan has to be looked for. */
 size_t dd_footprint_bytes(const dd_problem_desc* desc, int32_t n_src);
+/* The same without those plans, which a problem builds only in solves of its own: the bound of
+ * one that takes its solves in a batch. */
+size_t dd_batch_footprint_bytes(const dd_problem_desc* desc, int32_t n_src);
 
 /* eps, sigma: FEM-node arrays (float32, n_fem_nodes each) on the device.
  * Enforces eq. epsilon_sigma_constraint: eps = 1, sigma = 0 on layers 0 and 1,
@@ -504,10 +507,11 @@ const char* dd_last_error(const dd_problem* p);
  * fused step (else DD_ERR_UNSUPPORTED); it has no other active job and is not used
  * outside the batch until its job is done; all buffers stay valid until then.  A batch is
  * driven from one host thread and one stream.  Storage for the saved forward is allocated
- * in dd_batch_submit (see dd_footprint_bytes); dd_batch_step allocates nothing. */
+ * in dd_batch_submit (see dd_batch_footprint_bytes); dd_batch_step allocates nothing. */
 typedef struct dd_batch dd_batch;
 /* hbm_budget: bytes (0 = no limit) that the problems with an active job may hold together,
- * each counted at dd_footprint_bytes(its descriptor, its job's sources); dd_batch_submit of a
+ * each counted at dd_batch_footprint_bytes(its descriptor, its job's sources) and the plans
+ * that solves of its own have built; dd_batch_submit of a
  * job that does not fit gives DD_ERR_STATE and changes nothing (like a full batch), and a
  * job's bytes are returned when it completes. */
 int dd_batch_create(int32_t max_slots, size_t hbm_budget, dd_batch** out);

@@ -13,7 +13,7 @@ ERRORS = {
 }
 
 EXPORTS = [
-    "dd_create", "dd_destroy", "dd_sizes", "dd_detector_nodes", "dd_footprint_bytes",
+    "dd_create", "dd_destroy", "dd_sizes", "dd_detector_nodes", "dd_footprint_bytes", "dd_batch_footprint_bytes",
     "dd_set_coefficients", "dd_forward", "dd_adjoint", "dd_gradient", "dd_error_string", "dd_last_error",
     "dd_profile_enable", "dd_profile_read", "dd_algorithmic_bytes", "dd_debug_fem_apply",
     "dd_batch_create", "dd_batch_destroy", "dd_batch_submit", "dd_batch_step", "dd_batch_poll",
@@ -125,6 +125,8 @@ def load():
                                       ctypes.POINTER(ctypes.c_int64)]
     lib.dd_footprint_bytes.argtypes = [ctypes.POINTER(ProblemDesc), ctypes.c_int32]
     lib.dd_footprint_bytes.restype = ctypes.c_size_t
+    lib.dd_batch_footprint_bytes.argtypes = [ctypes.POINTER(ProblemDesc), ctypes.c_int32]
+    lib.dd_batch_footprint_bytes.restype = ctypes.c_size_t
     lib.dd_set_coefficients.argtypes = [P, P, P, P]
     lib.dd_set_coefficients_async.argtypes = [P, P, P, P]
     lib.dd_coefficients_status.argtypes = [P, P]
@@ -174,7 +176,7 @@ def load():
     lib.dd_cga_update.argtypes = [P, P, P, P, P, P]
     lib.dd_cga_get_info.argtypes = [P, ctypes.POINTER(CgaInfo), P]
     for name in EXPORTS:
-        if name not in ("dd_footprint_bytes", "dd_error_string", "dd_last_error"):
+        if name not in ("dd_footprint_bytes", "dd_batch_footprint_bytes", "dd_error_string", "dd_last_error"):
             getattr(lib, name).restype = ctypes.c_int
     _lib = lib
     return lib

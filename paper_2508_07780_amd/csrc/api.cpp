@@ -134,6 +134,7 @@ struct dd_problem {
   ResDevice res_fwd, res_adj;
   ResCtl* res_ctl = nullptr;
   double* res_tab = nullptr;
+  size_t res_bytes = 0;         // device bytes of all this
   bool res_ready = false;       // the control block has been cleared
   // launches called off, written by the GPU (host memory); how many the host knows of; solves still to run by launches
   // for it, and how many it will be next time; an event after the last resident solve
@@ -856,10 +857,12 @@ bool res_wanted(dd_problem* p, bool adj, int n_src, bool again, hipStream_t st) 
   if (!r.tried && (p->res_mode > 0 || p->graph == DD_GRAPH_ON || 1000 * (r.asked - (again ? 0 : 100)) >= p->N)) {
     r.tried = true;
     const std::string err = p->err;
+    const size_t held = p->alloc_bytes;
     if (res_create(p, adj, r, st) != DD_OK) {
       (void)hipGetLastError();
       p->err = err;
     }
+    p->res_bytes += p->alloc_bytes - held;
   }
   if (!r.n_blocks) return false;
   // The GPU is shared with work that leaves the blocks no place: launches for a while, longer each time (a call that finds no
@@ -1326,7 +1329,7 @@ std::string build_incidence(const HostMesh& m, std::vector<uint16_t>& inc, std::
 
 extern "C" {
 
-size_t dd_footprint_bytes(const dd_problem_desc* desc, int32_t n_src) {
+size_t dd_batch_footprint_bytes(const dd_problem_desc* desc, int32_t n_src) {
   if (!check_desc(desc).empty() || n_src < 0) return 0;
   const int64_t N = (int64_t)desc->n_outer[0] * desc->n_outer[1] * desc->n_outer[2];
   const int64_t fs[3] = {desc->fem_cells[0] + 1, desc->fem_cells[1] + 1, desc->fem_cells[2] + 1};
@@ -1362,6 +1365,7 @@ size_t dd_footprint_bytes(const dd_problem_desc* desc, int32_t n_src) {
   b += 4 * (4 * n_part + n_part * box) + 4 * STENCIL_SLOTS_MAX * 14;
   b += 4 * 4 * n_own;                     // eps - 1, c1, c2, sigma
   b += 4 * 6 * N;                         // E (2 levels) on the grid
+  b += 4 * 4 * FD_PAD;                    // the four levels' last quads
   b += 4 * 6 * N + 4 * (int64_t)ntiles;   // two more levels and the near-tile list (two-step launches)
   b += 4 * 9 * n_own;                     // E (2 levels) + V on the FEM nodes
   b += 4 * 6 * n_l0;                      // interface ring
@@ -1369,16 +1373,23 @@ size_t dd_footprint_bytes(const dd_problem_desc* desc, int32_t n_src) {
   b += (int64_t)n_src * ((nt + 1) * 3 * n_l0 * 4 + (n_ck + tail_levels) * 6 * n_own * 4);  // saved forward
   if (nseg > 1) b += (K + 1) * 6 * n_own * 4;  // recompute window
   if (nseg > 2) b += (K + 1) * 6 * n_own * 4;  // the second one (two segments in flight)
-  // resident solves: brick lists and exchange words, the pulse
-  b += resident_bytes_bound(*desc, device_cus(), false, false) + 8 * nt + 1024;
-  b += resident_bytes_bound(*desc, device_cus(), true, nseg > 1);
   // optional buffers: misfit partials and weights; FEM-node map and sum of the div-div
   // gradient terms (R2 / paper-formula gradient); initial data and its level-0 rows; a CGA run
   b += 8 * 1024 + 8 * nt;
   b += (4 + 8) * n_fem;
-  b += 2 * 4 * (3 * N + FD_PAD) + 8 * n_fem;
+  b += 2 * 4 * 3 * N + 8 * n_fem;
   b += (2 * 4 + 2 * 8) * n_fem + 8 * 6 * 1024 + 1024;
   return (size_t)b;
+}
+
+size_t dd_footprint_bytes(const dd_problem_desc* desc, int32_t n_src) {
+  const size_t b = dd_batch_footprint_bytes(desc, n_src);
+  if (!b) return 0;
+  // resident solves: brick lists and exchange words, the pulse
+  const bool rec = desc->n_steps > effective_ckpt_every(desc);
+  const int cus = device_cus();
+  const size_t plans = resident_bytes_bound(*desc, cus, false, false) + resident_bytes_bound(*desc, cus, true, rec);
+  return plans ? b + plans + 8 * (size_t)desc->n_steps + 1024 : b;
 }
 
 namespace {
@@ -2511,7 +2522,7 @@ int dd_batch_submit(dd_batch* b, dd_problem* p, const dd_source* src, int32_t n_
     const std::string e = check_source(p, src[s]);
     if (!e.empty()) return fail(p, DD_ERR_INVALID_ARG, e);
   }
-  const size_t bytes = dd_footprint_bytes(&p->d, n_src);
+  const size_t bytes = dd_batch_footprint_bytes(&p->d, n_src) + p->res_bytes;
   if (b->hbm_budget && b->in_use + bytes > b->hbm_budget)
     return fail(p, DD_ERR_STATE, "the job does not fit the batch's HBM budget (" + std::to_string(bytes) + " bytes, " +
                                      std::to_string(b->hbm_budget - std::min(b->in_use, b->hbm_budget)) + " free)");

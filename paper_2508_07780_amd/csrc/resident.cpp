@@ -572,23 +572,29 @@ bool resident_fits(const dd_problem_desc& d, int cus) {
 size_t resident_bytes_bound(const dd_problem_desc& d, int cus, bool adj, bool rec) {
   Cut fd, fe;
   if (!choose(d, cus, adj, rec, fd, fe)) return 0;
-  const auto rim = [](const Cut& c) {
-    const int64_t x = c.dim[0], y = c.dim[1], z = c.dim[2];
-    return x * y * z - std::max<int64_t>(x - 2, 0) * std::max<int64_t>(y - 2, 0) * std::max<int64_t>(z - 2, 0);
-  };
   const int64_t n[3] = {d.n_outer[0], d.n_outer[1], d.n_outer[2]};
-  const int64_t bricks = fd.blocks / 3, f[3] = {d.fem_cells[0] - 1, d.fem_cells[1] - 1, d.fem_cells[2] - 1};
+  const int64_t f[3] = {d.fem_cells[0] - 1, d.fem_cells[1] - 1, d.fem_cells[2] - 1};   // owned nodes
+  // nodes on either side of the planes between bricks
+  const auto between = [](const int64_t* n, const Cut& c) {
+    return 2 * ((c.num[0] - 1) * n[1] * n[2] + (c.num[1] - 1) * n[0] * n[2] + (c.num[2] - 1) * n[0] * n[1]);
+  };
   const int64_t own = f[0] * f[1] * f[2];
-  const auto faces = [](int64_t x, int64_t y, int64_t z) { return 2 * (x * y + y * z + x * z); };
-  const int64_t pub = bricks * rim(fd) + fe.blocks * rim(fe);
-  const int64_t con = bricks * faces(fd.dim[0], fd.dim[1], fd.dim[2]) + faces(f[0], f[1], f[2]) +
-                      fe.blocks * ((int64_t)(fe.dim[0] + 2) * (fe.dim[1] + 2) * (fe.dim[2] + 2) -
-                                   (int64_t)fe.dim[0] * fe.dim[1] * fe.dim[2]);
-  const int64_t det = face_lex_count(d.n_outer[0], d.n_outer[1], d.n_outer[2], d.detector_faces);
-  const int64_t l0 = face_lex_count(d.fem_cells[0] + 1, d.fem_cells[1] + 1, d.fem_cells[2] + 1, 63u);
-  int64_t b = (int64_t)sizeof(ResBlock) * (fd.blocks + fe.blocks) + 8 * faces(n[0], n[1], n[2]);
-  b += 2 * pub + 12 * con + 8 * (det + l0) + 8 * own;
-  b += (int64_t)8 * 3 * RES_RING * pub * (rec ? 2 : 1) + 4096;
+  const int64_t layer1 = own - std::max<int64_t>(f[0] - 2, 0) * std::max<int64_t>(f[1] - 2, 0) * std::max<int64_t>(f[2] - 2, 0);
+  const int64_t layer0 = face_lex_count(d.fem_cells[0] + 1, d.fem_cells[1] + 1, d.fem_cells[2] + 1, 63u);
+  const int64_t bricks = fd.blocks / 3;
+  // published: beside the cuts, and between the two regions
+  const int64_t pub = between(n, fd) + layer0 + between(f, fe) + layer1;
+  // collected: beside the cuts (and by a brick of a node of its own that a finite-element brick updates), the boxes'
+  // rims, and a word for its order by a brick from a finite-element brick that reads it
+  const int64_t con = between(n, fd) + layer1 + fe.blocks * ((int64_t)(fe.dim[0] + 2) * (fe.dim[1] + 2) * (fe.dim[2] + 2) -
+                                                             (int64_t)fe.dim[0] * fe.dim[1] * fe.dim[2]) +
+                      (int64_t)bricks * fe.blocks;
+  const unsigned sides = DD_FACE_XMIN | DD_FACE_XMAX | DD_FACE_YMIN | DD_FACE_YMAX;
+  const unsigned special = (d.absorbing_faces & sides) | (adj ? d.detector_faces : 0u);
+  const int64_t sp = face_lex_count(d.n_outer[0], d.n_outer[1], d.n_outer[2], special);
+  const int64_t out = adj ? 0 : face_lex_count(d.n_outer[0], d.n_outer[1], d.n_outer[2], d.detector_faces) + layer0;
+  int64_t b = (int64_t)sizeof(ResBlock) * (fd.blocks + fe.blocks) + 8 * (sp + out + own) + 2 * pub + 12 * con;
+  b += (int64_t)8 * 3 * RES_RING * pub * (rec ? 2 : 1) + 1024;     // and the lists' alignment, the control block
   return (size_t)b;
 }
 

@@ -4,7 +4,8 @@ Jobs arrive over time.  Each job is a sequence of reconstruction iterations of o
 problem (box "CGA": forward, misfit adjoint, eps/sigma gradient, then the conjugate
 gradient update of eps and sigma on the device); the problem's fields stay resident
 between its solves.  A job is admitted
-when a batch slot is free and its device footprint (dd_footprint_bytes plus its trace,
+when a batch slot is free and its device footprint (dd_batch_footprint_bytes, or dd_footprint_bytes
+of a job that runs alone, plus its trace,
 observation and gradient buffers) fits in the HBM budget; admitted solves join the
 running batch at the next launch, so work of jobs of different sizes overlaps on the
 device.  A job whose single step already fills the GPU (at least `solo_cells` cells per
@@ -98,13 +99,14 @@ class _Job:
         self.problem.close()
 
 
-def job_footprint(req):
+def job_footprint(req, alone=False):
+    """Device bytes of a request's job; alone: it runs through the single-problem calls."""
     w = req.workload
     n_src = len(w.sources)
     traces = n_src * int(w.desc.n_steps) * _n_det(w.desc) * 3 * 4
     # the problem (its CGA run included), traces and observations, gradients (FP64), the
     # iterate (float32) and the run's copy of it
-    return Problem.footprint_bytes(w.desc, n_src) + 2 * traces + (16 + 8 + 8) * w.desc.n_fem_nodes()
+    return Problem.footprint_bytes(w.desc, n_src, batched=not alone) + 2 * traces + (16 + 8 + 8) * w.desc.n_fem_nodes()
 
 
 def _n_det(desc):
@@ -268,10 +270,10 @@ def serve_batched(requests, max_slots=16, hbm_budget=None, chunk=256, time_fn=ti
         now = time_fn() - t0
         # admission: arrived, a slot free, the footprint fits
         while pending and pending[0].arrival <= now and len(active) < max_slots:
-            fp = job_footprint(pending[0])
+            alone = solo_cells is not None and step_cells(pending[0].workload.desc) >= solo_cells
+            fp = job_footprint(pending[0], alone)
             if fp > hbm_budget:
                 raise ValueError(f"request {pending[0].rid} needs {fp} bytes, over the HBM budget of {hbm_budget}")
-            alone = solo_cells is not None and step_cells(pending[0].workload.desc) >= solo_cells
             free_slot = next((sl for sl in slots if sl["thread"] is None), None)
             if alone and (free_slot is None or (active and not solo_overlap)):
                 break                    # solo_slots such jobs at a time (arrival order is kept)

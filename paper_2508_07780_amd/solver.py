@@ -114,9 +114,12 @@ class Problem:
             pass
 
     @staticmethod
-    def footprint_bytes(desc, n_src):
+    def footprint_bytes(desc, n_src, batched=False):
+        """Bound of a problem's device bytes; batched: of one that takes its solves in a Batch."""
         c = _lib.make_desc(desc)
-        return int(_lib.load().dd_footprint_bytes(ctypes.byref(c), int(n_src)))
+        lib = _lib.load()
+        f = lib.dd_batch_footprint_bytes if batched else lib.dd_footprint_bytes
+        return int(f(ctypes.byref(c), int(n_src)))
 
     @staticmethod
     def detector_nodes(desc):
