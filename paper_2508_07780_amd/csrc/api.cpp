@@ -136,7 +136,13 @@ struct dd_problem {
   double* res_tab = nullptr;
   size_t res_bytes = 0;         // device bytes of all this
   bool res_ready = false;       // the control block has been cleared
-  // launches called off, written by the GPU (host memory); how many the host knows of; solves still to run by launches
+  std::vector<double> res_pulse;   // a source's pulse, before its upload
+  // pinned memory that the plans' lists go up from (the second plan's from the first one's where that is large enough and
+  // has gone up), and an event after the last upload
+  unsigned char* res_host[2] = {nullptr, nullptr};
+  size_t res_host_size = 0;
+  hipEvent_t res_up = nullptr;
+  // launches called off, written by the GPU (the head of res_host[0]); how many the host knows of; solves still to run by launches
   // for it, and how many it will be next time; an event after the last resident solve
   int* res_off = nullptr;
   int res_off_seen = 0;
@@ -682,6 +688,13 @@ struct CaptureRelaxed {
   ~CaptureRelaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
 };
 
+// Whether an event's work is known to be over (under CaptureRelaxed).
+bool event_over(hipEvent_t e) {
+  const hipError_t q = hipEventQuery(e);
+  if (q == hipErrorNotReady && hipPeekAtLastError() == hipErrorNotReady) (void)hipGetLastError();
+  return q == hipSuccess;
+}
+
 // The resident launches in flight per GPU (resident_order.hpp).  Another process's can still be in the way: then the
 // launch's own protocol decides.
 struct ResOrder {
@@ -708,11 +721,7 @@ struct ResQueue {
     const CaptureRelaxed relaxed;
     counts = o->flights.admit(
         st, blocks, device_cus(),
-        [](hipEvent_t e) {
-          const hipError_t q = hipEventQuery(e);
-          if (q == hipErrorNotReady && hipPeekAtLastError() == hipErrorNotReady) (void)hipGetLastError();
-          return q == hipSuccess;
-        },
+        [](hipEvent_t e) { return event_over(e); },
         [&](hipEvent_t e) { (void)hipStreamWaitEvent(st, e, 0); },
         [&](hipEvent_t e) {
           if (end) (void)hipEventDestroy(e);
@@ -727,64 +736,84 @@ struct ResQueue {
   }
 };
 
-// A brick plan and its lists on the device, in one allocation and one copy.  Without memory for them the problem's
-// solves go on by launches.
+// A brick plan, its lists, its words and (with the problem's first plan) the control block and the pulse on the device, in one
+// allocation, which without memory for it fails as a whole: the problem's solves then go on by launches.  The lists go up from pinned
+// memory, kept until dd_destroy, in stream order: the call does not wait for the stream, and calls nothing that a capture
+// of another thread forbids.
 int res_create(dd_problem* p, bool adj, ResDevice& r, hipStream_t st) {
+  const CaptureRelaxed relaxed;
   const bool rec = adj && n_segments(p) > 1;
   ResPlan& q = r.plan;
   build_resident(p->d, p->res_own_api, device_cus(), adj, rec, q);
   if (q.blocks.empty()) return DD_OK;
-  r.a.n_blocks = (int)q.blocks.size();
-  r.a.n_pub = q.n_pub;
+  p->res_pulse.reserve(p->d.n_steps);
+  for (hipEvent_t* e : {&p->res_end, &p->res_up})
+    if (!*e && hipEventCreateWithFlags(e, hipEventDisableTiming) != hipSuccess)
+      return fail(p, DD_ERR_HIP, "event creation failed");
+  ResArgs a{};
+  a.n_blocks = (int)q.blocks.size();
+  a.n_pub = q.n_pub;
   const StarValues& v = p->star;
-  r.a.sk1 = v.k1; r.a.sk6 = v.k6; r.a.sb1 = v.b1; r.a.sb2 = v.b2; r.a.sb4 = v.b4; r.a.sb6 = v.b6; r.a.sb12 = v.b12;
-  std::vector<unsigned char> all;
-  unsigned char* dev = nullptr;
-  size_t at = 0;
-  const auto put = [&](const auto& list, auto& ptr) {
-    const size_t bytes = list.size() * sizeof(list[0]);
-    if (dev) {
-      ptr = reinterpret_cast<std::remove_reference_t<decltype(ptr)>>(dev + at);
-      if (bytes) std::memcpy(all.data() + at, list.data(), bytes);
-    }
+  a.sk1 = v.k1; a.sk6 = v.k6; a.sb1 = v.b1; a.sb2 = v.b2; a.sb4 = v.b4; a.sb6 = v.b6; a.sb12 = v.b12;
+  ResCtl* ctl = p->res_ctl;
+  double* tab = p->res_tab;
+  constexpr size_t kHead = 64;                 // host: the word of called-off launches
+  unsigned char *dev = nullptr, *host = nullptr;
+  size_t at = 0, lists = 0;
+  const auto place = [&](size_t bytes, auto& ptr) {
+    if (dev) ptr = reinterpret_cast<std::remove_reference_t<decltype(ptr)>>(dev + at);
     at += (bytes + 15) / 16 * 16;
   };
-  for (int pass = 0; pass < 2; ++pass) {       // the size, then the places
+  const auto put = [&](const auto& list, auto& ptr) {
+    const size_t bytes = list.size() * sizeof(list[0]);
+    if (dev && bytes) std::memcpy(host + kHead + at, list.data(), bytes);
+    place(bytes, ptr);
+  };
+  for (int pass = 0; pass < 2; ++pass) {       // the sizes, then the places
     at = 0;
-    put(q.blocks, r.a.blocks);
-    put(q.sp_meta, r.a.sp_meta);
-    put(q.sp_det, r.a.sp_det);
-    put(q.pub_cell, r.a.pub_cell);
-    put(q.con_word, r.a.con_word);
-    put(q.con_step, r.a.con_step);
-    put(q.con_cell, r.a.con_cell);
-    put(q.con_src, r.a.con_src);
-    put(q.out_cell, r.a.out_cell);
-    put(q.out_idx, r.a.out_idx);
-    put(q.fem_node, r.a.fem_node);
+    put(q.blocks, a.blocks);
+    put(q.sp_meta, a.sp_meta);
+    put(q.sp_det, a.sp_det);
+    put(q.pub_cell, a.pub_cell);
+    put(q.con_word, a.con_word);
+    put(q.con_step, a.con_step);
+    put(q.con_cell, a.con_cell);
+    put(q.con_src, a.con_src);
+    put(q.out_cell, a.out_cell);
+    put(q.out_idx, a.out_idx);
+    put(q.fem_node, a.fem_node);
+    lists = at;
+    const size_t words = sizeof(unsigned long long) * RES_RING * 3 * q.n_pub;
+    place(words, a.xbuf);
+    if (rec) place(words, a.xbuf_rec);
+    if (!p->res_ctl) place(sizeof(ResCtl), ctl);
+    if (!p->res_tab) place(sizeof(double) * p->d.n_steps, tab);
     if (pass) break;
-    if (int rc = dalloc(p, &dev, at)) return rc;
-    all.resize(at);
-  }
-  if (int rc = dalloc(p, &r.a.xbuf, (size_t)RES_RING * 3 * q.n_pub)) return rc;
-  if (rec)
-    if (int rc = dalloc(p, &r.a.xbuf_rec, (size_t)RES_RING * 3 * q.n_pub)) return rc;
-  if (!p->res_end && hipEventCreateWithFlags(&p->res_end, hipEventDisableTiming) != hipSuccess)
-    return fail(p, DD_ERR_HIP, "event creation failed");
-  if (!p->res_off) {
-    if (hipHostMalloc((void**)&p->res_off, sizeof(int), hipHostMallocDefault) != hipSuccess) {
-      p->res_off = nullptr;
-      return fail(p, DD_ERR_OOM, "host allocation failed");
+    if (p->res_host_size >= kHead + lists && event_over(p->res_up)) {
+      host = p->res_host[0];
+    } else {
+      const int k = p->res_host[0] ? 1 : 0;
+      const size_t bytes = kHead + lists + (k ? 0 : lists);    // an adjoint's lists are up to twice a forward's
+      if (hipHostMalloc((void**)&p->res_host[k], bytes, hipHostMallocDefault) != hipSuccess) {
+        p->res_host[k] = nullptr;
+        return fail(p, DD_ERR_OOM, "host allocation failed");
+      }
+      host = p->res_host[k];
+      if (!k) {
+        p->res_host_size = bytes;
+        p->res_off = reinterpret_cast<int*>(host);
+        *p->res_off = 0;
+      }
     }
-    *p->res_off = 0;
+    if (int rc = dalloc(p, &dev, at)) return rc;
   }
-  if (!p->res_ctl)
-    if (int rc = dalloc(p, &p->res_ctl, 1)) return rc;
-  if (!p->res_tab)
-    if (int rc = dalloc(p, &p->res_tab, p->d.n_steps)) return rc;
-  if (hipMemcpyAsync(dev, all.data(), at, hipMemcpyHostToDevice, st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess)
+  if (hipMemcpyAsync(dev, host + kHead, lists, hipMemcpyHostToDevice, st) != hipSuccess ||
+      hipEventRecord(p->res_up, st) != hipSuccess)
     return fail(p, DD_ERR_HIP, "hipMemcpy upload failed");
-  r.n_blocks = r.a.n_blocks;
+  p->res_ctl = ctl;
+  p->res_tab = tab;
+  r.a = a;
+  r.n_blocks = a.n_blocks;
   ResPlan kept;                                 // what the launches read
   kept.adj = adj;
   kept.rec = rec;
@@ -856,12 +885,17 @@ bool res_wanted(dd_problem* p, bool adj, int n_src, bool again, hipStream_t st) 
   r.asked = std::min(r.asked + (int64_t)n_src * p->d.n_steps, p->N + 100);
   if (!r.tried && (p->res_mode > 0 || p->graph == DD_GRAPH_ON || 1000 * (r.asked - (again ? 0 : 100)) >= p->N)) {
     r.tried = true;
-    const std::string err = p->err;
     const size_t held = p->alloc_bytes;
-    if (res_create(p, adj, r, st) != DD_OK) {
-      (void)hipGetLastError();
-      p->err = err;
+    int rc = DD_ERR_OOM;
+    std::string err;
+    err.swap(p->err);
+    try {
+      rc = res_create(p, adj, r, st);
+    } catch (...) {             // no host memory: by launches
     }
+    err.swap(p->err);
+    if (rc != DD_OK) (void)hipGetLastError();
+    if (!r.n_blocks) r.plan = ResPlan();
     p->res_bytes += p->alloc_bytes - held;
   }
   if (!r.n_blocks) return false;
@@ -910,7 +944,8 @@ int res_forward(dd_problem* p, const dd_source& src, int s, float* traces, bool 
     a.tail = p->tail[s];
   }
   // the pulse at every step up to its last nonzero value
-  std::vector<double> tab;
+  std::vector<double>& tab = p->res_pulse;
+  tab.clear();
   if (!sp.oblique)
     for (int n = 0; n < p->d.n_steps; ++n) {
       const double v = source_time(src, (double)n * dt);
@@ -1622,11 +1657,13 @@ int dd_destroy(dd_problem* p) {
   if (p->aux) (void)hipStreamDestroy(p->aux);
   graph_free(p->gfwd);
   graph_free(p->gadj);
-  if (p->res_end) {
-    (void)hipEventSynchronize(p->res_end);
-    (void)hipEventDestroy(p->res_end);
-  }
-  if (p->res_off) (void)hipHostFree(p->res_off);
+  for (hipEvent_t e : {p->res_end, p->res_up})
+    if (e) {
+      (void)hipEventSynchronize(e);
+      (void)hipEventDestroy(e);
+    }
+  for (unsigned char* host : p->res_host)
+    if (host) (void)hipHostFree(host);
   if (p->cap) (void)hipStreamDestroy(p->cap);
   for (void* q : p->allocs) raw_free(p->free_fn, p->actx, q);
   delete p;
