@@ -2027,8 +2027,9 @@ int dd_check_finite(dd_problem* p, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   int h_err = 0;
   if (hipMemsetAsync(p->d_err, 0, sizeof(int), st) != hipSuccess) return fail(p, DD_ERR_HIP, "hipMemsetAsync failed");
+  const FdArgs f = fd_base(p);
   for (int b = 0; b < 4; ++b)
-    if (p->Efd[b]) launch_count_nonfinite(p->Efd[b], 3 * p->N, p->d_err, st);
+    if (p->Efd[b]) launch_count_nonfinite_grid(p->Efd[b], p->d.n_outer, f.blo, f.bhi, p->d_err, st);
   for (int b = 0; b < 2; ++b) launch_count_nonfinite(p->Efem[b], 3 * p->n_own, p->d_err, st);
   launch_count_nonfinite(p->Vfem, 3 * p->n_own, p->d_err, st);
   if (int rc = check_launch(p)) return rc;

@@ -339,6 +339,7 @@ void launch_tikhonov_add(const float* em1, const float* sig_own, const int* own_
 void launch_gradient_out(const double* g_eps, const double* g_sig, const int* own_api, const int* own_grid,
                          int64_t n_own, double* out_eps, double* out_sig, hipStream_t s);
 void launch_count_nonfinite(const float* x, int64_t n, int* err, hipStream_t s);
+void launch_count_nonfinite_grid(const float* x, const int n[3], const int blo[3], const int bhi[3], int* err, hipStream_t s);
 
 // ---- host-side mesh and partitions ----------------------------------------------------
 

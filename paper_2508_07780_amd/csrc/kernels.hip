@@ -1820,6 +1820,20 @@ __global__ void count_nonfinite_kernel(const float* x, int64_t n, int* err) {
   if (bad) atomicAdd(err, bad);
 }
 
+// The same of a grid field [3][nz][ny][nx] without the nodes inside the box's layer 1: no step reads or writes them, and what an
+// earlier solve left there is no part of the state.
+__global__ void count_nonfinite_grid_kernel(const float* x, int nx, int ny, int nz, int bx, int by, int bz, int ex, int ey,
+                                            int ez, int* err) {
+  const int64_t N = (int64_t)nx * ny * nz;
+  int bad = 0;
+  for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < N; g += (int64_t)gridDim.x * blockDim.x) {
+    const int i = (int)(g % nx), j = (int)((g / nx) % ny), k = (int)(g / ((int64_t)nx * ny));
+    if (i > bx + 1 && i < ex - 1 && j > by + 1 && j < ey - 1 && k > bz + 1 && k < ez - 1) continue;
+    for (int c = 0; c < 3; ++c) bad += !isfinite(x[c * N + g]);
+  }
+  if (bad) atomicAdd(err, bad);
+}
+
 static int grid_for(int64_t n, int block = 256, int cap = 4096) {
   int64_t g = (n + block - 1) / block;
   if (g < 1) g = 1;
@@ -2118,6 +2132,11 @@ void launch_gradient_out(const double* g_eps, const double* g_sig, const int* ow
 
 void launch_count_nonfinite(const float* x, int64_t n, int* err, hipStream_t s) {
   if (n > 0) hipLaunchKernelGGL(count_nonfinite_kernel, dim3(grid_for(n)), dim3(256), 0, s, x, n, err);
+}
+
+void launch_count_nonfinite_grid(const float* x, const int n[3], const int blo[3], const int bhi[3], int* err, hipStream_t s) {
+  hipLaunchKernelGGL(count_nonfinite_grid_kernel, dim3(grid_for((int64_t)n[0] * n[1] * n[2])), dim3(256), 0, s, x, n[0], n[1],
+                     n[2], blo[0], blo[1], blo[2], bhi[0], bhi[1], bhi[2], err);
 }
 
 // ---------------------------------------------------------------------------------------
