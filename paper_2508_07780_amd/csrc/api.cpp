@@ -955,7 +955,7 @@ int res_forward(dd_problem* p, const dd_source& src, int s, float* traces, bool 
       }
     }
   a.n_tab = (int)tab.size();
-  launch_resident_begin(a, s == 0, tab.data(), a.n_tab, st);
+  launch_resident_begin(a, false, s == 0, tab.data(), a.n_tab, st);
   launch_resident(a, p->res_fwd.plan, st);
   launch_resident_rest(a, fd_base(p), fem_base(p), false, st);
   return check_launch(p);
@@ -977,7 +977,7 @@ int res_adjoint(dd_problem* p, int s, const float* cot, const float* obs, hipStr
   const FemArgs f = fem_base(p);
   a.inv_dt2 = f.inv_dt2;
   a.inv_2dt = f.inv_2dt;
-  launch_resident_begin(a, s == 0, nullptr, 0, st);
+  launch_resident_begin(a, true, s == 0, nullptr, 0, st);
   launch_resident(a, p->res_adj.plan, st);
   launch_resident_rest(a, fd_base(p), f, true, st);
   return check_launch(p);

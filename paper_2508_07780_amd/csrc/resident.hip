@@ -327,7 +327,7 @@ __device__ __forceinline__ void fd_brick(const ResArgs& a, const ResBlock& b, fl
   exchange_lists<false>(a, b, b.con_n, xc);
   for (int i = t; i < SZ * (b.dim[2] + 2); i += RES_THREADS) L[i] = 0.f;
   if (t == 0) given_up = 0;
-  const unsigned tag0 = a.ctl->epoch;
+  const unsigned tag0 = a.ctl->epoch[ADJ];
   if (!ADJ && a.ihist)   // layer-0 values of level 0
     for (int e = t; e < b.out_n; e += RES_THREADS)
       if (a.out_cell[b.out_off + e] >> 16) a.ihist[comp * a.n_l0 + a.out_idx[b.out_off + e]] = 0.f;
@@ -657,7 +657,7 @@ __device__ __forceinline__ void fem_forward(const ResArgs& a, const ResBlock& b,
         if (a.k_tail == 0) a.tail[c * n_own + f.own[j]] = 0.f;
       }
   }
-  const unsigned tag0 = a.ctl->epoch;
+  const unsigned tag0 = a.ctl->epoch[0];
   __syncthreads();
   for (int n = 0; n < nt; ++n) {
     fem_advance(a, f, box, sx, sxy, V);
@@ -748,7 +748,7 @@ __device__ __forceinline__ void fem_adjoint(const ResArgs& a, const ResBlock& b,
     ge[j] = a.g_eps[own];
     gs[j] = a.g_sig[own];
   }
-  const unsigned tag0 = a.ctl->epoch;
+  const unsigned tag0 = a.ctl->epoch[1];
   unsigned tag_rec = tag0;
   const int n_rim0 = b.con_n - b.con_fem;      // layer-0 nodes of the rim
   __syncthreads();
@@ -933,9 +933,9 @@ __global__ __launch_bounds__(RES_THREADS) void resident_kernel(ResArgs a) {
 }
 
 struct TabChunk { double v[RES_TAB]; };
-__global__ void resident_begin_kernel(ResCtl* c, int tags, bool first, double* tab, int off, int n, TabChunk v) {
+__global__ void resident_begin_kernel(ResCtl* c, bool adj, int tags, bool first, double* tab, int off, int n, TabChunk v) {
   if (off == 0 && threadIdx.x == 0) {
-    c->epoch += tags;
+    c->epoch[adj] += tags;
     c->arrive = c->end = 0;
     c->tickets = c->finished = 0;
     if (first) c->skip = 0;
@@ -951,13 +951,13 @@ void launch_t(const ResArgs& a, size_t lds, hipStream_t s) {
 
 }  // namespace
 
-void launch_resident_begin(const ResArgs& a, bool first, const double* tab, int n, hipStream_t s) {
+void launch_resident_begin(const ResArgs& a, bool adj, bool first, const double* tab, int n, hipStream_t s) {
   int off = 0;
   do {
     TabChunk v;
     const int m = std::min(n - off, RES_TAB);
     for (int i = 0; i < m; ++i) v.v[i] = tab[off + i];
-    hipLaunchKernelGGL(resident_begin_kernel, dim3(1), dim3(512), 0, s, a.ctl, 2 * a.nt + 64, first, const_cast<double*>(a.tab), off,
+    hipLaunchKernelGGL(resident_begin_kernel, dim3(1), dim3(512), 0, s, a.ctl, adj, 2 * a.nt + 64, first, const_cast<double*>(a.tab), off,
                        m, v);
     off += m;
   } while (off < n);

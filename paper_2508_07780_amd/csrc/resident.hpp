@@ -8,8 +8,9 @@
 // is small against its volume; finite-element bricks hold all three.
 //
 // Exchange: one 8-byte word per published node and component, {value, tag}, stored and polled
-// with relaxed agent-scope atomics; the tag is the level's number, unique over the problem's
-// solves, so a word tells by itself whether it is the awaited level, and no flag or fence
+// with relaxed agent-scope atomics; the tag is the level's number, unique over the plan's
+// solves (a direction has its own words and numbers: however often the other one runs, a word holds a tag of its plan's last
+// solve, which the next one never awaits), so a word tells by itself whether it is the awaited level, and no flag or fence
 // follows the data.  Words sit in a ring of two levels.  Bricks collect from each other mutually, so a
 // block that publishes level n+2 has collected the level n+1 of each of its readers, which they published after
 // collecting level n: the level n words it overwrites have been read.
@@ -77,7 +78,7 @@ __host__ __device__ inline ResRows res_rows(const int* dim, int run, int t) {
 }
 
 struct ResCtl {
-  unsigned epoch;              // tag of level 0 of the current solve
+  unsigned epoch[2];           // tag of level 0 of the direction's current solve
   int arrive, state, end;      // RES_WAIT .. RES_DONE
   unsigned long long tickets, finished;   // of the last resort
   int skip;                    // a launch of this call has been called off: its other solves go to the last resort
@@ -174,7 +175,7 @@ bool resident_fits(const dd_problem_desc& d, int cus);
 size_t resident_bytes_bound(const dd_problem_desc& d, int cus, bool adj, bool rec);
 
 // first: the call's first solve.
-void launch_resident_begin(const ResArgs& a, bool first, const double* tab, int n, hipStream_t s);
+void launch_resident_begin(const ResArgs& a, bool adj, bool first, const double* tab, int n, hipStream_t s);
 void launch_resident(const ResArgs& a, const ResPlan& plan, hipStream_t s);
 // The last resort: takes all steps unless the solve is done (kernels.hip).
 void launch_resident_rest(const ResArgs& a, const FdArgs& fa, const FemArgs& ea, bool adj, hipStream_t s);
