@@ -142,8 +142,8 @@ struct dd_problem {
   unsigned char* res_host[2] = {nullptr, nullptr};
   size_t res_host_size = 0;
   hipEvent_t res_up = nullptr;
-  // launches called off, written by the GPU (the head of res_host[0]); how many the host knows of; solves still to run by launches
-  // for it, and how many it will be next time; an event after the last resident solve
+  // launches called off, written by the GPU (the head of res_host[0]); how many the host knows of; solves still to run
+  // by launches for it, and how many it will be next time; an event after the last resident solve
   int* res_off = nullptr;
   int res_off_seen = 0;
   int64_t res_pause = 0, res_pause_next = 16;
@@ -736,10 +736,10 @@ struct ResQueue {
   }
 };
 
-// A brick plan, its lists, its words and (with the problem's first plan) the control block and the pulse on the device, in one
-// allocation, which without memory for it fails as a whole: the problem's solves then go on by launches.  The lists go up from pinned
-// memory, kept until dd_destroy, in stream order: the call does not wait for the stream, and calls nothing that a capture
-// of another thread forbids.
+// A brick plan, its lists, its words and (with the problem's first plan) the control block and the pulse on the device,
+// in one allocation, which without memory for it fails as a whole: the problem's solves then go on by launches.  The
+// lists go up from pinned memory, kept until dd_destroy, in stream order: the call does not wait for the stream, and
+// calls nothing that a capture of another thread forbids.
 int res_create(dd_problem* p, bool adj, ResDevice& r, hipStream_t st) {
   const CaptureRelaxed relaxed;
   const bool rec = adj && n_segments(p) > 1;
@@ -899,8 +899,8 @@ bool res_wanted(dd_problem* p, bool adj, int n_src, bool again, hipStream_t st) 
     p->res_bytes += p->alloc_bytes - held;
   }
   if (!r.n_blocks) return false;
-  // The GPU is shared with work that leaves the blocks no place: launches for a while, longer each time (a call that finds no
-  // place costs about the launches' time for the wait and two to five times it for its solves).
+  // The GPU is shared with work that leaves the blocks no place: launches for a while, longer each time (a call that
+  // finds no place costs about the launches' time for the wait and two to five times it for its solves).
   const int off = __atomic_load_n(p->res_off, __ATOMIC_RELAXED);
   if (off != p->res_off_seen) {
     p->res_off_seen = off;

@@ -327,8 +327,8 @@ __device__ __forceinline__ void fd_tile(const FdArgs& a, const int b) {
 }
 
 // ---------------------------------------------------------------------------------------
-// The same update of one component, four nodes along x per thread (all steps but those with energies and
-// those beside element partitions).  A block takes 256 consecutive quads of the (row, quad of the row) order of a plane, so
+// The same update of one component, four nodes along x per thread (steps without energies and not beside element
+// partitions; small grids keep the tile where it is faster, rows_pay).  A block takes 256 consecutive quads of the (row, quad of the row) order of a plane, so
 // that rows of any length leave no lane idle but in the last block, and row_zc(NT) planes.  No LDS and no
 // barrier: the neighbours along x are the next lanes' (a wave's end lanes load theirs), the rows above and
 // below are read again (they are in the caches: a block's own rows, or its neighbour's on the same XCD), and all loads of a block are on
@@ -336,7 +336,7 @@ __device__ __forceinline__ void fd_tile(const FdArgs& a, const int b) {
 // Bound by instructions on grids whose fields the last-level cache holds (about 350 per wave of two planes), by HBM on larger ones.
 // us per forward step, the 32 x 8 tile of one node per thread (bound by its instructions: each node's
 // addresses, LDS accesses and flags) -> this: 117x106x121 17.1 -> 13.8, 128^3 (FEM 32^3) 18.0 -> 14.4, 160^3 32.0 -> 26.6,
-// 192^3 (FEM 96^3) 59.0 -> 51.4, 224^3 88.9 -> 76.7, 288^3 174.8 -> 149.3 (5.8 TB/s by the kernel's minimum).
+// 192^3 (FEM 96^3) 59.0 -> 51.4, 224^3 88.9 -> 76.7, 288^3 174.8 -> 149.3 (5.8 TB/s by the bytes that it cannot do without).
 // Planes per block, us per step at 128^3 / 160^3: 1 16.5 / 31.2, 2 15.0 / 27.4, 3 16.0 / 28.2, 4 (one loaded ahead: all would be
 // too many registers) 15.8 / 27.9; streaming, at 224^3 / 288^3: 2 80.2 / 152, 3 77.1 / 149, 4 78.9 / 155, 8 80.3 / 159.  All three
 // components in a block, to share the addresses: the compiler keeps all of it in registers (170 to 260).
@@ -1820,8 +1820,8 @@ __global__ void count_nonfinite_kernel(const float* x, int64_t n, int* err) {
   if (bad) atomicAdd(err, bad);
 }
 
-// The same of a grid field [3][nz][ny][nx] without the nodes inside the box's layer 1: no step reads or writes them, and what an
-// earlier solve left there is no part of the state.
+// The same of a grid field [3][nz][ny][nx] without the nodes inside the box's layer 1: no step reads or writes them,
+// and what an earlier solve left there is no part of the state.
 __global__ void count_nonfinite_grid_kernel(const float* x, int nx, int ny, int nz, int bx, int by, int bz, int ex, int ey,
                                             int ez, int* err) {
   const int64_t N = (int64_t)nx * ny * nz;
@@ -2140,15 +2140,16 @@ void launch_count_nonfinite_grid(const float* x, const int n[3], const int blo[3
 }
 
 // ---------------------------------------------------------------------------------------
-// A resident solve's last resort (resident.hpp), where its launch was called off: the steps by the tiles and partitions of
-// the step kernels, in one launch of any number of blocks, of which any number may be on the GPU.  Blocks take
-// tickets in the order of the work; a ticket's work waits until all work of the steps before is done.  That
-// was given out earlier, to blocks that are running and wait for yet earlier work only: every wait ends, with one block
-// as with all of them.  Work is handed from block to block through memory: one wave's fences of the GPU's scope around
-// each ticket's, which bound a step: one block per CU, and few, large tickets.  us per step, forward / adjoint, with a block
-// per CU: 25^3 11.5 / 12.2 (by launches 5.5 / 5.9), 37x35x41 with recompute 18.9 / 25.8 (5.1 / 8.3), 64^3 32.6 / 31.1 (6.6 /
-// 6.6), 96^3 with recompute 53.7 / 74.6 (10.6 / 13.2); with two blocks per CU and twice the tickets 15.7 / 16.0, 35.9 / 42.9, 58.6 /
-// 54.7, 85.7 / 116.8; fences by all waves 90 / 96 at 64^3; one block for everything 157 / 180, 272 / 319, 1620 / 1799, 3746 / 5049.
+// A resident solve's last resort (resident.hpp), where its launch was called off: the steps by the tiles and
+// partitions of the step kernels, in one launch of any number of blocks, of which any number may be on the GPU.
+// Blocks take tickets in the order of the work; a ticket's work waits until all work of the steps before is done.
+// That was given out earlier, to blocks that are running and wait for yet earlier work only: every wait ends, with
+// one block as with all of them.  Work is handed from block to block through memory: one wave's fences of the GPU's
+// scope around each ticket's, which bound a step: one block per CU, and few, large tickets.  us per step, forward /
+// adjoint, with a block per CU: 25^3 11.5 / 12.2 (by launches 5.5 / 5.9), 37x35x41 with recompute 18.9 / 25.8 (5.1 /
+// 8.3), 64^3 32.6 / 31.1 (6.6 / 6.6), 96^3 with recompute 53.7 / 74.6 (10.6 / 13.2); with two blocks per CU and twice
+// the tickets 15.7 / 16.0, 35.9 / 42.9, 58.6 / 54.7, 85.7 / 116.8; fences by all waves 90 / 96 at 64^3; one block for
+// everything 157 / 180, 272 / 319, 1620 / 1799, 3746 / 5049.
 // ---------------------------------------------------------------------------------------
 constexpr int REST_TICKETS = 128;   // of a step: for its partitions, and for its row blocks, at most
 constexpr int REST_CHUNKS = 64;     // tickets of a fill or copy

@@ -2,10 +2,9 @@
 //
 // A step costs compute, publish and collect with a barrier between them: the exchange's round trip through the
 // memory side (1.15 us for a few words per block, 1.5 us for three per thread) plus the longest brick's
-// compute, bound by vector and LDS instructions of one block per CU.  By launches a step costs the launch and its drain, 5.5
-// us and more.  us per step, forward / adjoint with checkpoints recomputed, by launches -> resident: 25^3 5.5 -> 2.6 (forward);
-// 37x35x41 5.5 / 9.2 -> 3.2 / 6.0; 48^3 5.9 / 7.7 -> 3.3 / 5.9; 64^3 6.7 / 9.5 -> 4.1 / 6.8; 96^3 (FEM 48^3)
-// 12.0 / 16.6 -> 7.1 / 11.2.
+// compute, bound by vector and LDS instructions of one block per CU.  By launches a step costs the launch and its drain,
+// 5 us and more.  us per step, forward / adjoint, by launches -> resident: 25^3 5.5 / 5.9 -> 2.7 / 4.0; with checkpoints
+// recomputed 37x35x41 5.0 / 8.4 -> 2.9 / 5.7, 64^3 6.5 / 7.7 -> 4.0 / 6.2, 96^3 (FEM 48^3) 10.5 / 13.1 -> 7.2 / 10.3.
 #include "resident.hpp"
 
 #include <algorithm>

@@ -9,18 +9,18 @@
 //
 // Exchange: one 8-byte word per published node and component, {value, tag}, stored and polled
 // with relaxed agent-scope atomics; the tag is the level's number, unique over the plan's
-// solves (a direction has its own words and numbers: however often the other one runs, a word holds a tag of its plan's last
-// solve, which the next one never awaits), so a word tells by itself whether it is the awaited level, and no flag or fence
-// follows the data.  Words sit in a ring of two levels.  Bricks collect from each other mutually, so a
+// solves (a direction has its own words and numbers: however often the other one runs, a word holds a tag of its
+// plan's last solve, which the next one never awaits), so a word tells by itself whether it is the awaited level, and
+// no flag or fence follows the data.  Words sit in a ring of two levels.  Bricks collect from each other mutually, so a
 // block that publishes level n+2 has collected the level n+1 of each of its readers, which they published after
 // collecting level n: the level n words it overwrites have been read.
 //
 // Blocks wait for each other, so all of them must be on the GPU at once.  Each announces
 // itself first, and the last one to arrive starts the solve for all; if some do not get a place
 // in time (the GPU is shared with other work), the launch is called off before anything is
-// written, and a kernel that needs no number of blocks at once takes all steps, at about the launches' rate.  The
-// state is decided by compare-and-swap, so every block sees the same outcome; waits during the solve are bounded the
-// same way.
+// written, and a kernel that needs no number of blocks at once takes all steps, in two to five times the launches'
+// time.  The state is decided by compare-and-swap, so every block sees the same outcome; waits during the solve are
+// bounded the same way.
 #pragma once
 
 #include "dd_common.hpp"

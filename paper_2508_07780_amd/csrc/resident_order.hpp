@@ -10,9 +10,9 @@
 namespace dd {
 
 // The newest resident launch of each stream that may still run, oldest first.  An entry counts for everything that may
-// run until its event: its own blocks, or those of what it waits for that has no entry of its own any more (the stream's launch
-// before it, an entry taken out to make room).  Entries that are waited for stay: what comes later may still
-// meet them.  So of any launches that run together, the newest saw all others listed and found room beside them.
+// run until its event: its own blocks, or those of what it waits for that has no entry of its own any more (the
+// stream's launch before it, an entry taken out to make room).  Entries that are waited for stay: what comes later may
+// still meet them.  So of any launches that run together, the newest saw all others listed and found room beside them.
 template <class Stream, class Event>
 struct ResFlights {
   struct Entry {
@@ -24,8 +24,8 @@ struct ResFlights {
   Entry e[kMost];
   int n = 0;
 
-  // Before a launch of `blocks` blocks is queued on `st`; add() follows with the value returned.  done(event): known to be over;
-  // wait(event): the stream waits for it; drop(event): not needed any more.
+  // Before a launch of `blocks` blocks is queued on `st`; add() follows with the value returned.  done(event): known to
+  // be over; wait(event): the stream waits for it; drop(event): not needed any more.
   template <class Done, class Wait, class Drop>
   int admit(Stream st, int blocks, int cus, Done&& done, Wait&& wait, Drop&& drop) {
     int mine = 0;      // blocks that may run before this launch and have no entry
