@@ -3,6 +3,7 @@
 * every variant of the resident kernels takes its solves itself, and equals the launches;
 * a called-off launch's solves are taken by the fallback kernel, at a rate near the launches';
 * launches of unequal sizes on several streams are not called off;
+* solves beside work that fills the GPU;
 * a solve whose launch is called off, with the streaming variant of the launches forced
   (DD_FD_NT=1): the kernel that takes it lays out its own blocks.
 """
@@ -153,3 +154,33 @@ def test_launches_for_a_while_after_a_call_off(monkeypatch):
     assert sum(t != (0, 0) for t in tries) == 3
     p.close()
     ref.close()
+
+
+def test_beside_work_that_fills_the_gpu(monkeypatch):
+    """Solves on one stream while large products keep the GPU full on another: whichever kernel takes a solve, its results
+    are the launches'."""
+    import torch
+    form = problem("cube64")
+    form[0].n_steps = form[0].ckpt_every = 60
+    ref = _problem(torch, monkeypatch, form, 0)
+    want = _run(torch, ref, form[3])
+    ref.close()
+    p = _problem(torch, monkeypatch, form, 1)
+    a = torch.randn((8192, 8192), device="cuda")
+    c = torch.empty_like(a)
+    other, mine = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(other):
+        for _ in range(40):
+            torch.mm(a, a, out=c)
+        end = torch.cuda.Event()
+        end.record()
+    with torch.cuda.stream(mine):
+        for _ in range(4):
+            got = _run(torch, p, form[3])
+            assert all(_same(torch, got, want)), _same(torch, got, want)
+        stats = [p.resident_stats(w) for w in ("forward", "adjoint")]
+    print(f"[gpu] {stats}", flush=True)
+    for s, n in zip(stats, (_solves(2)["forward"], _solves(2)["adjoint"])):
+        assert s["solves"] + s["fallback"] <= 4 * n and s["called_off"] <= s["fallback"]
+    p.close()
