@@ -708,13 +708,14 @@ ResOrder& res_order() {
   return order[dev & 63];
 }
 // Held while a call queues resident launches of `blocks` blocks on `st`, which first waits for those that leave it no
-// room.
+// room.  However the call ends, `mark` is recorded after what it has queued: dd_destroy waits for that (the launches
+// write to the problem's host word).
 struct ResQueue {
   ResOrder* o = nullptr;
   hipStream_t st;
-  hipEvent_t end = nullptr;
+  hipEvent_t mark, end = nullptr;
   int counts = 0;
-  ResQueue(int blocks, hipStream_t s) : st(s) {
+  ResQueue(int blocks, hipStream_t s, hipEvent_t m) : st(s), mark(m) {
     if (!blocks) return;
     o = &res_order();
     o->lock.lock();
@@ -730,6 +731,7 @@ struct ResQueue {
   }
   ~ResQueue() {
     if (!o) return;
+    (void)hipEventRecord(mark, st);
     if ((end || hipEventCreateWithFlags(&end, hipEventDisableTiming) == hipSuccess) && hipEventRecord(end, st) == hipSuccess)
       o->flights.add(st, end, counts);
     o->lock.unlock();
@@ -910,11 +912,6 @@ bool res_wanted(dd_problem* p, bool adj, int n_src, bool again, hipStream_t st) 
   if (p->res_pause <= 0 || p->res_mode == 2) return true;
   p->res_pause -= n_src;
   return false;
-}
-
-// After the resident solves of a call: dd_destroy waits for them (they write to the problem's host word).
-int res_mark(dd_problem* p, hipStream_t st) {
-  return hipEventRecord(p->res_end, st) == hipSuccess ? DD_OK : fail(p, DD_ERR_HIP, "event record failed");
 }
 
 int res_forward(dd_problem* p, const dd_source& src, int s, float* traces, bool save, hipStream_t st) {
@@ -1745,7 +1742,7 @@ int dd_forward(dd_problem* p, const dd_source* src, int32_t n_src, float* traces
   std::vector<unsigned char> key = forward_key(p, src, n_src, traces_dev, save != 0, energy_dev);
   const bool again = call_again(p, p->gfwd, key), res = !energy_dev && res_wanted(p, false, n_src, again, st);
   key_put(key, res);
-  ResQueue order(res ? p->res_fwd.n_blocks : 0, st);
+  ResQueue order(res ? p->res_fwd.n_blocks : 0, st, p->res_end);
   if (res) res_prepare(p, p->res_fwd, st);
   if (graph_wanted(p, p->gfwd, key, again)) {
     int rc = graph_run(p, p->gfwd, key, st, [&](hipStream_t cs) {
@@ -1763,8 +1760,6 @@ int dd_forward(dd_problem* p, const dd_source* src, int32_t n_src, float* traces
       if (rc) return rc;
     }
   }
-  if (res)
-    if (int rc = res_mark(p, st)) return rc;
   if (save) {
     p->saved = true;
     p->saved_n_src = n_src;
@@ -1798,7 +1793,7 @@ int adjoint_all(dd_problem* p, const float* cot, const float* obs, hipStream_t s
   // stream had drained
   const bool again = call_again(p, p->gadj, key), res = !p->pg_on && res_wanted(p, true, p->saved_n_src, again, st);
   key_put(key, res);
-  ResQueue order(res ? p->res_adj.n_blocks : 0, st);
+  ResQueue order(res ? p->res_adj.n_blocks : 0, st, p->res_end);
   if (res) res_prepare(p, p->res_adj, st);
   if (n_segments(p) == 1 && graph_wanted(p, p->gadj, key, again)) {
     int rc = graph_run(p, p->gadj, key, st, [&](hipStream_t cs) {
@@ -1814,8 +1809,6 @@ int adjoint_all(dd_problem* p, const float* cot, const float* obs, hipStream_t s
     int rc = adjoint_launches(p, cot, obs, res, st);
     if (rc) return rc;
   }
-  if (res)
-    if (int rc = res_mark(p, st)) return rc;
   p->have_grad = true;
   p->have_pg = p->pg_on || p->r2;
   return DD_OK;
